@@ -122,9 +122,8 @@ struct WallMot {
 template <typename S, class L, typename PsiN, typename RefN>
 __device__ __forceinline__ void collide_push(const Prm<ArT<S>> &p, const S *sv, ArT<S> rin, PsiN psin, RefN refn,
                                              ArT<S> psi0, ArT<S> rown, S *__restrict__ fout, uint32_t solid_dirs,
-                                             int x, int y, int z,
-                                             long long Np, const cell_t *__restrict__ mask,
-                                             const WallMot *wm) {
+                                             int x, int y, int z, long long Np, const WallMot *wm,
+                                             ArT<S> *__restrict__ rho_link) {
     using T = ArT<S>;
     const int nx = p.nx, ny = p.ny, nz = p.nz;
     const uint32_t idx = (uint32_t)(x + nx * (y + ny * z));
@@ -134,6 +133,14 @@ __device__ __forceinline__ void collide_push(const Prm<ArT<S>> &p, const S *sv, 
 
     T f[L::Q];
     sfor<L::Q>([&](auto I) { f[I] = pop_get<S>(sv[I], Dir<decltype(I)::value, L>::template w<T>(), rin); });
+    // the density of a node with links, summed in the order of the directions, for the moving-wall term
+    // of the force scan, which would read the q populations again for it
+    if constexpr (!wall_in_fluid_pass<S>())
+        if (solid_dirs) {
+            T r = T(0);
+            sfor<L::Q>([&](auto I) { r += f[I]; });
+            stb(rho_link, idx * (uint32_t)sizeof(T), r);
+        }
     // moments from pair sums and differences
     T rho = f[0], jx = T(0), jy = T(0), jz = T(0);
     sfor<(L::Q - 1) / 2>([&](auto K) {
@@ -354,7 +361,7 @@ __device__ __forceinline__ ArT<S> node_psi_of(const Prm<ArT<S>> &p, const BodyDe
 template <typename S, class L, int TY>
 __global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<ArT<S>> p, const S *__restrict__ fin,
                                                                      S *__restrict__ fout, ArT<S> *__restrict__ psi,
-                                                                     const ArT<S> *__restrict__ psi_prev,
+                                                                     ArT<S> *__restrict__ psi_prev,
                                                                      const cell_t *__restrict__ mask, BodyDev *bodies,
                                                                      int parity, StepState *st,
                                                                      const ClassifyPart *__restrict__ cpart, int cblk,
@@ -576,7 +583,7 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<A
                     collide_push<S, L>(
                         p, cur, rin, [&](auto I) { return win_psi<S>(nbr(I)); },
                         [&](auto I) { return win_ref<S>(nbr(I)); }, psi0, win_ref<S>(*r0), fout, solid_dirs, x,
-                        y0 + ty, z, plane_stride(), mask, wall_mot());
+                        y0 + ty, z, plane_stride(), wall_mot(), psi_prev);
                 }
             }
             cm[r] = A[r].m;
@@ -599,18 +606,76 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<A
 //    and -f on b2 at q; only nodes within r_c of a higher-index body's solid radius search.
 // Torques are about the body centres X_b (minimum image).  Each wave reduces its contributions
 // per touched body (64-lane shuffles) into LDS in a fixed order and every block writes FP64
-// partials [body * 6 + component][block], summed by the first advection sweep (k_advect), which
-// also advances the bodies.
-// waves per block of the force scan (one block per CU), sized so that the gathered link values
-// (reflected populations and link forces of every direction) stay in registers: 8 on D3Q19, 8 in
-// FP32 and 4 in FP64 on D3Q27
-template <typename T, class L>
-constexpr int force_waves() {
-    return L::Q == 19 ? 8 : (sizeof(T) == 4 ? 8 : 4);
+// partials [body * 6 + component][block], summed by the rigid-body update (k_tile_activity).
+//
+// What bounds it: each wave runs a chain of four or five dependent memory rounds once, so the
+// kernel is bound by latency and by the number of instructions on a wave's path (a SIMD holds one
+// or two waves here, which issue one instruction in four cycles at best, and code that every wave
+// runs once is fetched cold).  The work of one node is therefore split over lanes: the links of a
+// node over eight lanes, the offsets of the repulsion search over the whole wave, and the six sums
+// of a body share one exchange tree.  On large boxes the cache lines of the scattered nodes bound it,
+// so only the planes of real links are read and the density comes from the fluid pass.  Against one
+// lane per node with unrolled searches (67 KB of code, now 14 KB), in FP32 unless noted: 61 x 45 x 50
+// two spheres 15.7 -> 8.5 us, 128^3 two spheres 18.7 -> 13.9 (D3Q27 25.1 -> 16.2), 256^3 four spheres
+// 42.9 -> 27.1 (FP16 storage 31.4 -> 27.4), 32^3 plates FP64 37.6 -> 23.0.
+constexpr int FORCE_WAVES = 12;  // waves per block of the force scan (one block per CU)
+
+// component d of direction i known only at run time, from two-bit fields
+__device__ __forceinline__ int dir_rt(int i, int d) {
+    constexpr auto pack = [](const int *c) {
+        unsigned long long v = 0;
+        for (int k = 0; k < 27; ++k) v |= (unsigned long long)(c[k] + 1) << (2 * k);
+        return v;
+    };
+    constexpr unsigned long long X = pack(kCX), Y = pack(kCY), Z = pack(kCZ);
+    return (int)(((d == 0 ? X : (d == 1 ? Y : Z)) >> (2 * i)) & 3u) - 1;
+}
+
+// periodic wrap by repeated addition (usually none; several on an axis shorter than the offset)
+__device__ __forceinline__ int wrapl(int i, int n) {
+    while (i < 0) i += n;
+    while (i >= n) i -= n;
+    return i;
+}
+
+// Totals of six values over a wave, in a fixed order: three halving exchanges leave each lane one
+// component's sum over the 8 lanes that share its low bits, three more finish it.  Lane l returns
+// the total of component l >> 3 (0..5; 0 for 6 and 7).
+__device__ __forceinline__ double wave_sum6(const double (&v)[6]) {
+    const int lane = (int)(threadIdx.x & 63);
+    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
+    double a[4], b[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double up = j < 2 ? v[(4 + j) % 6] : 0.0;
+        a[j] = (h5 ? up : v[j]) + __shfl_xor(h5 ? v[j] : up, 32, 64);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b[j] = (h4 ? a[2 + j] : a[j]) + __shfl_xor(h4 ? a[j] : a[2 + j], 16, 64);
+    double c = (h3 ? b[1] : b[0]) + __shfl_xor(h3 ? b[0] : b[1], 8, 64);
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    return c;
+}
+
+// s plus m times the values that eight lanes hold of directions 1 + q, 9 + q, .. (v[k] of lane q:
+// direction 1 + q + 8 k), added in the order of the directions with one rounding each, in each of
+// the lanes
+template <int Q, typename T, int NS>
+__device__ __forceinline__ T ordered_sum(T s, const T (&v)[NS], T m) {
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        const T x = __shfl(v[(i - 1) / 8], (i - 1) % 8, 8);
+        if constexpr (sizeof(T) == 8)
+            s = __builtin_fma(x, m, s);
+        else
+            s = __builtin_fmaf(x, m, s);
+    }
+    return s;
 }
 
 template <typename S, class L>
-__global__ __launch_bounds__((64 * force_waves<ArT<S>, L>())) void k_body_forces(Prm<ArT<S>> p, int parity,
+__global__ __launch_bounds__(64 * FORCE_WAVES) void k_body_forces(Prm<ArT<S>> p, int parity,
                                                      const StepState *st, const S *__restrict__ fin,
                                                      S *__restrict__ fpost, const ArT<S> *__restrict__ psi,
                                                      const ArT<S> *__restrict__ psi_prev,
@@ -618,339 +683,297 @@ __global__ __launch_bounds__((64 * force_waves<ArT<S>, L>())) void k_body_forces
                                                      const BodyDev *__restrict__ bodies, double *part,
                                                      const uint32_t *__restrict__ nbw) {
     using T = ArT<S>;
-    constexpr int W = force_waves<T, L>(), NT = 64 * W;
+    constexpr int W = FORCE_WAVES, NT = 64 * W;
     __shared__ double acc[W][PF_LBM_MAX_BODIES][6];
-    __shared__ double bt[W][PF_LBM_MAX_BODIES][9];  // X, V, W of every body
+    __shared__ double bt[PF_LBM_MAX_BODIES][10];  // X, V, W and psi of every body
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nbod = p.nb;
-    // each wave clears and fills only its own row of the sums and reads its own copy of the body
-    // motion (loaded here, off the dependent chain of the scan): no barrier before the scan
-    for (int k = lane; k < PF_LBM_MAX_BODIES * 6; k += 64) (&acc[wave][0][0])[k] = 0.0;
-    for (int k = lane; k < nbod * 9; k += 64) {
-        const BodyDev &B = bodies[k / 9];
-        const int c = k % 9;
-        bt[wave][k / 9][c] = c < 3 ? B.X[c] : (c < 6 ? B.V[c - 3] : B.W[c - 6]);
+    // each wave clears and fills only its own row of the sums
+    for (int k = lane; k < nbod * 6; k += 64) (&acc[wave][0][0])[k] = 0.0;
+    if (tid < nbod * 10) {
+        const BodyDev &B = bodies[tid / 10];
+        const int c = tid % 10;
+        bt[tid / 10][c] = c < 3 ? B.X[c] : (c < 6 ? B.V[c - 3] : (c < 9 ? B.W[c - 6] : B.psi_s));
     }
-    __builtin_amdgcn_wave_barrier();
+    __syncthreads();
     const BoxIter it(st->box[parity], p.nx, p.ny, p.nz);
     const int nx = p.nx, ny = p.ny, nz = p.nz;
     const long long Np = p.Np;
     const bool rep = nbod > 1 && (p.flags & PF_LBM_REPULSION);
-    const double rc = p.r_c;
-    constexpr int RC = 32;  // repulsion offsets per round of loads
-    // Each wave takes U rows of 64 consecutive box cells, the rows nw * 64 cells apart (nw waves in
-    // the grid), so that the cells with work -- clustered on the bodies' surfaces and, for the
-    // repulsion, in the small caps where two bodies nearly touch -- spread over all waves.  A first
-    // pass loads the U cell words of each lane in one round and keeps the cells that need the
-    // per-link (or repulsion) work: fluid cells with a solid neighbour, and solid cells within r_c of
-    // the solid radius of a higher-index body.  The second pass runs that work on the kept cells
-    // only, 64 per round, so the cells without a link cost one load in a wide round each.
-    constexpr int U = 8;
-    __shared__ int keep[W][64 * U];
-    __shared__ double rsum[W][9][64];  // per-lane repulsion sums of the current round
+    // offset of a point from the centre of body b (minimum image)
+    auto lever = [&](int b, const int *c, double *r) {
+        const double *BX = bt[b];
+        r[0] = mimg_r(c[0] - BX[0], nx, p.inv_n[0]);
+        r[1] = mimg_r(c[1] - BX[1], ny, p.inv_n[1]);
+        r[2] = mimg_r(c[2] - BX[2], nz, p.inv_n[2]);
+    };
+    // the totals of one body over the wave into its sums
+    auto add = [&](int b, const double (&v)[6]) {
+        const double s = wave_sum6(v);
+        if ((lane & 7) == 0 && lane < 48) acc[wave][b][lane >> 3] += s;
+    };
+    // A wave takes U rounds of 64 box cells, in runs of RUN consecutive cells, the runs nw * RUN cells
+    // apart (nw waves in the grid), so that the cells with work -- clustered on the bodies'
+    // surfaces and, for the repulsion, in the small caps where two bodies nearly touch -- spread
+    // over all waves.  A first pass loads the cell words of the U rounds together and keeps the
+    // cells that need work: from the front of the list the fluid cells with a solid neighbour, from
+    // its back the solid cells within r_c of the solid radius of a higher-index body.  (Runs of 64
+    // cells: 11.9 instead of 8.5 us at 61 x 45 x 50, 41.9 instead of 23.0 on the 32^3 plates.)
+    constexpr int U = 4, CAP = 64 * U, RUN = 16, RPW = 64 / RUN;
+    __shared__ int keep[W][CAP];
     const int gw = (int)blockIdx.x * W + wave, nw = (int)gridDim.x * W;
-    for (int run = gw * 64; run < it.vol; run += nw * 64 * U) {
-        int nkeep = 0;
+    // cell of this lane in round u of the runs that start at s0, and the first cell of the round
+    auto cell_of = [&](long long s0, int u) { return ((s0 + u * RPW + lane / RUN) * nw + gw) * RUN + (lane & (RUN - 1)); };
+    for (long long s0 = 0; (s0 * nw + gw) * RUN < it.vol; s0 += RPW * U) {
+        int nlink = 0, nrepc = 0;
         {
             cell_t wk[U];
-            int ck[U][3];
-            bool in[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = run + nw * 64 * u + lane;
-                in[u] = k < it.vol;
-                int uu[3];
-                it.cell(in[u] ? k : 0, uu, ck[u]);
-                wk[u] = in[u] ? mask[ck[u][0] + nx * (ck[u][1] + ny * ck[u][2])] : cell_t(C_SOLID);
-            }
             uint32_t nbk[U];
+            // rounds past the end of the box are skipped by the whole wave
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if constexpr (L::kBits)
-                    nbk[u] = wk[u] & C_NBMASK;
-                else
-                    nbk[u] = (in[u] && !(wk[u] & C_SOLID)) ? nbw[ck[u][0] + nx * (ck[u][1] + ny * ck[u][2])] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                bool need = false;
-                if (in[u]) {
-                    if (!(wk[u] & C_SOLID)) {
-                        need = nbk[u] != 0;
-                    } else if (rep) {
-                        const int o1 = owner_of(wk[u]);
-                        for (int b2 = o1 + 1; b2 < nbod; ++b2) {
-                            const double *BX = bt[wave][b2];
-                            const double rx = mimg_r(ck[u][0] - BX[0], nx, p.inv_n[0]),
-                                         ry = mimg_r(ck[u][1] - BX[1], ny, p.inv_n[1]),
-                                         rz = mimg_r(ck[u][2] - BX[2], nz, p.inv_n[2]);
-                            if (sqrt(rx * rx + ry * ry + rz * rz) < (double)st->srad[b2] + rc + 1e-3) need = true;
-                        }
+                wk[u] = nbk[u] = 0;
+                if (((s0 + RPW * u) * nw + gw) * RUN < it.vol) {
+                    const long long k = cell_of(s0, u);
+                    if (k < it.vol) {
+                        int uu[3], c[3];
+                        it.cell((int)k, uu, c);
+                        const int idx = c[0] + nx * (c[1] + ny * c[2]);
+                        wk[u] = mask[idx];
+                        if constexpr (!L::kBits) nbk[u] = nbw[idx];
                     }
                 }
-                const uint64_t bal = __ballot(need);
-                if (need) keep[wave][nkeep + __popcll(bal & ((1ull << lane) - 1ull))] = run + nw * 64 * u + lane;
-                nkeep += __popcll(bal);
+            }
+#pragma unroll 1
+            for (int u = 0; u < U; ++u) {
+                const cell_t w = u == 0 ? wk[0] : (u == 1 ? wk[1] : (u == 2 ? wk[2] : wk[3]));
+                const uint32_t nb = u == 0 ? nbk[0] : (u == 1 ? nbk[1] : (u == 2 ? nbk[2] : nbk[3]));
+                const int k = (int)cell_of(s0, u);
+                const bool solid = (w & C_SOLID) != 0;
+                const bool link = !solid && (L::kBits ? w & C_NBMASK : nb) != 0;
+                const uint64_t bal = __ballot(link);
+                if (link) keep[wave][nlink + __popcll(bal & ((1ull << lane) - 1ull))] = k;
+                nlink += __popcll(bal);
+                if (rep && __ballot(solid)) {
+                    bool need = false;
+                    if (solid) {
+                        int uu[3], c[3];
+                        it.cell(k, uu, c);
+                        for (int b2 = owner_of(w) + 1; b2 < nbod; ++b2) {
+                            double r[3];
+                            lever(b2, c, r);
+                            const double reach = (double)st->srad[b2] + p.r_c + 1e-3;
+                            need = need || r[0] * r[0] + r[1] * r[1] + r[2] * r[2] < reach * reach;
+                        }
+                    }
+                    const uint64_t bas = __ballot(need);
+                    if (need) keep[wave][CAP - 1 - nrepc - __popcll(bas & ((1ull << lane) - 1ull))] = k;
+                    nrepc += __popcll(bas);
+                }
             }
         }
         __builtin_amdgcn_wave_barrier();
-        for (int j0 = 0; j0 < nkeep; j0 += 64) {
-            const bool has = j0 + lane < nkeep;
-            const int k = has ? keep[wave][j0 + lane] : 0;
+        // links: eight lanes per node, lane q of them takes the directions 1 + q, 9 + q, ...
+        constexpr int NS = (L::Q + 6) / 8;
+        for (int j0 = 0; j0 < nlink; j0 += 8) {
+            // the lane's directions are formed anew in each round (opaque to the compiler, which would
+            // keep their components, weights and offsets in registers across the whole kernel)
+            int q = lane & 7;
+            asm volatile("" : "+v"(q));
+            const bool has = j0 + (lane >> 3) < nlink;
             uint32_t touched = 0;
-            int x = 0, y = 0, z = 0, idx = 0, b1 = -1;
-            // repulsion of a solid node p of body b1: the first body rb2 > b1 met in the search
-            int rb2 = -1;
-            bool rmulti = false;
-            uint32_t nbits = 0;  // solid-neighbour bits of a fluid node
-            bool fluid = false;
-            T rho = T(0), ps0 = T(0), rown = T(0), drho = T(0);
-            // per link i into a solid neighbour: its owner (4-bit fields), the reflected post-collision
-            // population fr_i = f*_i and the body-independent part of the link force, a_i = 2 f*_i +
+            int c[3] = {0, 0, 0};
+            uint32_t is = 0;
+            T rho = T(0), rown = T(0), drho = T(0), f0 = T(0);
+            // per link i into a solid neighbour: its owner (-1: no link), the reflected post-collision
+            // population fr = f*_i and the body-independent part of the link force, a = 2 f*_i +
             // G psi(x) w_i psi(x + c_i); drho sums the moving-wall terms of the node's links
-            uint32_t own[(L::Q + 7) / 8] = {};
-            T a[L::Q], fr[L::Q];
+            int own[NS];
+            T a[NS], fr[NS], fq[NS];
             if (has) {
-                int u[3], c[3];
-                it.cell(k, u, c);
-                x = c[0];
-                y = c[1];
-                z = c[2];
-                idx = x + nx * (y + ny * z);
-                const cell_t w0 = mask[idx];
-                if (!(w0 & C_SOLID)) {
-                    fluid = true;
-                    uint32_t mo[L::Q];  // words of the neighbours
-                    const NbrU ne(x, y, z, nx, ny, nz, 1);
-                    if constexpr (L::kBits)
-                        nbits = w0 & C_NBMASK;
+                int u[3];
+                it.cell(keep[wave][j0 + (lane >> 3)], u, c);
+                const uint32_t idx = (uint32_t)(c[0] + nx * (c[1] + ny * c[2]));
+                is = idx * (uint32_t)sizeof(S);
+                const NbrU ne(c[0], c[1], c[2], nx, ny, nz, 1);
+                uint32_t nbits;
+                if constexpr (L::kBits)
+                    nbits = mask[idx] & C_NBMASK;
+                else
+                    nbits = nbw[idx];
+                // The gathers of the node are issued in one round and unconditionally, so the
+                // per-link selects below wait for memory once; loads inside per-link branches were
+                // serialised, one memory latency per link.  A direction without a link reads the node's
+                // own word and rest population instead, so that no cache line is fetched for it (the
+                // lines bound this kernel on large boxes: each holds one or two of the scattered nodes).
+                // The psi of a solid neighbour is its owner's.
+                cell_t mo[NS];
+                S fo[NS], fi[NS + 1], fr0;
+                fr0 = ldb(fpost, is);
+                const T ps0 = psi[idx], pp = psi_prev[idx];
+                if constexpr (wall_in_fluid_pass<S>()) fi[NS] = ldb(fin, is);
+#pragma unroll
+                for (int k = 0; k < NS; ++k) {
+                    const int i = 1 + q + 8 * k;
+                    const bool on = i < L::Q;
+                    const int opp = (i & 1) ? i + 1 : i - 1;
+                    if constexpr (wall_in_fluid_pass<S>()) fi[k] = ldb(fin + (long long)(on ? i : 0) * Np, is);
+                    const int dx = dir_rt(i, 0), dy = dir_rt(i, 1), dz = dir_rt(i, 2);
+                    const bool link = on && (nbits & (1u << i));
+                    own[k] = link ? 0 : -1;
+                    fo[k] = ldb(fpost + (long long)(link ? opp : 0) * Np, is);
+                    const uint32_t n = link ? idx + (dx > 0 ? ne.xp : (dx < 0 ? ne.xm : 0u)) +
+                                                  (dy > 0 ? ne.yp : (dy < 0 ? ne.ym : 0u)) +
+                                                  (dz > 0 ? ne.zp : (dz < 0 ? ne.zm : 0u))
+                                            : idx;
+                    mo[k] = ldb(mask, n * 4u);
+                }
+                rown = sizeof(S) == 2 ? ref_density(ps0, p.rho0) : T(0);
+                f0 = pop_get<S>(fr0, Dir<0, L>::template w<T>(), rown);
+                // density of the node: left by the fluid pass, or (FP16) summed from its populations
+                if constexpr (!wall_in_fluid_pass<S>())
+                    rho = pp;
+                else
+                    rho = ref_density(pp, p.rho0) + (T)fi[NS];
+                const T gp = p.G * ps0;
+#pragma unroll
+                for (int k = 0; k < NS; ++k) {
+                    const int i = 1 + q + 8 * k;
+                    if constexpr (wall_in_fluid_pass<S>()) fq[k] = (T)fi[k];
+                    if (own[k] >= 0) own[k] = owner_of(mo[k]) & (PF_LBM_MAX_BODIES - 1);
+                    touched |= own[k] >= 0 ? 1u << own[k] : 0u;
+                    const int c2 = i <= 6 ? 1 : (i <= 18 ? 2 : 3);
+                    const T w = T(L::wshell[1]) * T(c2 == 1) + T(L::wshell[2]) * T(c2 == 2) + T(L::wshell[3]) * T(c2 == 3);
+                    // reflected value: f*_i, or f*_i + g_i where the fluid pass added g
+                    fr[k] = pop_get<S>(fo[k], w, rown);
+                    const T ps = (T)bt[max(own[k], 0)][9];
+                    if constexpr (sizeof(S) == 2)
+                        a[k] = __builtin_fmaf(gp * w, ps, T(2) * fr[k]);
                     else
-                        nbits = nbw[idx];
-                    if (nbits) {
-                        // Every gather of the node is issued in one round and unconditionally (the
-                        // neighbour values are cache-served), so the per-link selects below wait for
-                        // memory once; loads inside the per-link branches were serialised, one
-                        // memory latency per link.
-                        const uint32_t ib = (uint32_t)idx * (uint32_t)sizeof(T);
-                        const uint32_t is = (uint32_t)idx * (uint32_t)sizeof(S);
-                        S fo[L::Q];  // reflected populations f*_i, in slot opp(i), written by the fluid pass
-                        T pn[L::Q];  // neighbour pseudopotentials
-                        sfor<L::Q>([&](auto I) {
-                            constexpr int i = decltype(I)::value;
-                            if constexpr (i > 0) {
-                                const uint32_t n = ne.template at<i>((uint32_t)idx);
-                                mo[i] = ldb(mask, n * 4u);
-                                fo[i] = ldb(fpost + (long long)Dir<i, L>::opp * Np, is);
-                                pn[i] = ldb(psi, n * (uint32_t)sizeof(T));
-                            }
-                        });
-                        rho = sizeof(S) == 2 ? ref_density(psi_prev[idx], p.rho0) : T(0);
-                        sfor<L::Q>([&](auto I) { rho += (T)ldb(fin + (long long)I * Np, is); });
-                        ps0 = ldb(psi, ib);
-                        rown = sizeof(S) == 2 ? ref_density(ps0, p.rho0) : T(0);
-                        const T gp = p.G * ps0;
-                        sfor<L::Q>([&](auto I) {
-                            constexpr int i = decltype(I)::value;
-                            a[i] = T(0);
-                            fr[i] = T(0);
-                            if constexpr (i > 0) {
-                                if (nbits & (1u << i)) {
-                                    const uint32_t o = (uint32_t)owner_of(mo[i]);
-                                    own[i >> 3] |= o << (4 * (i & 7));
-                                    touched |= 1u << o;
-                                    // reflected value: f*_i, or f*_i + g_i where the fluid pass added g
-                                    fr[i] = pop_get<S>(fo[i], Dir<i, L>::template w<T>(), rown);
-                                    a[i] = T(2) * fr[i] + gp * Dir<i, L>::template w<T>() * pn[i];
-                                }
-                            }
-                        });
-                    }
-                } else if (rep) {
-                    // a solid node of body b1 within r_c of the solid radius of a body b2 > b1 may
-                    // have solid nodes of b2 within r_c: both bodies are marked, and the per-body
-                    // pass below finds the pairs (a pair-free mark adds zeros)
-                    b1 = owner_of(w0);
-                    for (int b2 = b1 + 1; b2 < nbod; ++b2) {
-                        const double *BX = bt[wave][b2];
-                        const double rx = mimg_r(x - BX[0], nx, p.inv_n[0]), ry = mimg_r(y - BX[1], ny, p.inv_n[1]),
-                                     rz = mimg_r(z - BX[2], nz, p.inv_n[2]);
-                        if (sqrt(rx * rx + ry * ry + rz * rz) < (double)st->srad[b2] + rc + 1e-3)
-                            touched |= (1u << b1) | (1u << b2);
-                    }
-                    if (touched) {
-                        // one pass over the offsets within r_c: the force on b1 from every body
-                        // above it (rs1), and the reaction on the first such body met with its
-                        // lever-arm part sum d x f (rs2, rt2), kept in the lane's LDS slots for the
-                        // per-body loop; a second body met gets its reaction from a pass of its own
-                        double rs1[3] = {0.0, 0.0, 0.0}, rs2[3] = {0.0, 0.0, 0.0}, rt2[3] = {0.0, 0.0, 0.0};
-                        const int nrep = st->n_rep;
-                        for (int j0 = 0; j0 < nrep; j0 += RC) {
-                            cell_t mqs[RC];
-#pragma unroll
-                            for (int j = 0; j < RC; ++j) {
-                                const int o = st->rep_off[j0 + j < nrep ? j0 + j : j0];
-                                const int dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
-                                mqs[j] = mask[wrapi(x + dx, nx) + nx * (wrapi(y + dy, ny) + ny * wrapi(z + dz, nz))];
-                            }
-#pragma unroll
-                            for (int j = 0; j < RC; ++j) {
-                                if (j0 + j >= nrep) break;
-                                const cell_t mq = mqs[j];
-                                if (!(mq & C_SOLID)) continue;
-                                const int b2 = owner_of(mq);
-                                if (b2 <= b1) continue;
-                                rs1[0] += st->rep_f[j0 + j][0];
-                                rs1[1] += st->rep_f[j0 + j][1];
-                                rs1[2] += st->rep_f[j0 + j][2];
-                                if (rb2 < 0) rb2 = b2;
-                                if (b2 != rb2) {
-                                    rmulti = true;
-                                    continue;
-                                }
-                                const double fx = -1.0 * st->rep_f[j0 + j][0], fy = -1.0 * st->rep_f[j0 + j][1],
-                                             fz = -1.0 * st->rep_f[j0 + j][2];
-                                rs2[0] += fx;
-                                rs2[1] += fy;
-                                rs2[2] += fz;
-                                const int o = st->rep_off[j0 + j];
-                                const double dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
-                                rt2[0] += dy * fz - dz * fy;
-                                rt2[1] += dz * fx - dx * fz;
-                                rt2[2] += dx * fy - dy * fx;
-                            }
-                        }
-                        for (int c = 0; c < 3; ++c) {
-                            rsum[wave][c][lane] = rs1[c];
-                            rsum[wave][3 + c][lane] = rs2[c];
-                            rsum[wave][6 + c][lane] = rt2[c];
-                        }
-                    }
+                        a[k] = T(2) * fr[k] + gp * w * ps;
                 }
             }
-            uint32_t wt = wave_or(touched);
-            while (wt) {
-                const int b = __ffs(wt) - 1;
-                wt &= wt - 1;
+            if constexpr (wall_in_fluid_pass<S>()) rho = ordered_sum<L::Q>(rho, fq, T(1));
+            for (int b = 0; b < nbod; ++b) {
+                if (!__ballot(touched & (1u << b))) continue;
                 double v[6] = {0, 0, 0, 0, 0, 0};
-                if ((touched & (1u << b)) && fluid) {
+                T gs[NS] = {};
+                if (touched & (1u << b)) {
                     // The link midpoint is x + c_i/2, so with r the node's offset from the centre:
                     // c_i . u_w(x + c_i/2) = c_i . u_w(x) (the term c_i . (W x c_i)/2 vanishes) and
                     // (r + c_i/2) x s c_i = r x s c_i.  The wall term needs the node's rigid velocity
                     // only, and the torque is r x (sum of the link forces).
-                    const double *BX = bt[wave][b], *BV = BX + 3, *BW = BX + 6;
-                    const double rx = mimg_r(x - BX[0], nx, p.inv_n[0]), ry = mimg_r(y - BX[1], ny, p.inv_n[1]),
-                                 rz = mimg_r(z - BX[2], nz, p.inv_n[2]);
-                    const double u0x = BV[0] + (BW[1] * rz - BW[2] * ry), u0y = BV[1] + (BW[2] * rx - BW[0] * rz),
-                                 u0z = BV[2] + (BW[0] * ry - BW[1] * rx);
-                    double fx = 0.0, fy = 0.0, fz = 0.0;
-                    sfor<L::Q>([&](auto I) {
-                        constexpr int i = decltype(I)::value;
-                        if constexpr (i > 0) {
-                            if ((nbits & (1u << i)) && ((own[i >> 3] >> (4 * (i & 7))) & 15u) == (uint32_t)b) {
-                                double cuw = 0.0;
-                                if constexpr (Dir<i, L>::x != 0) cuw += Dir<i, L>::x * u0x;
-                                if constexpr (Dir<i, L>::y != 0) cuw += Dir<i, L>::y * u0y;
-                                if constexpr (Dir<i, L>::z != 0) cuw += Dir<i, L>::z * u0z;
-                                // moving-wall term g: the reflected population becomes f*_i + g (Sec.
-                                // 3.2.2); the link carries 2 f*_i + g to the body plus the
-                                // pseudopotential reaction, both along c_i
-                                const T g = T(-6.0 * Dir<i, L>::template w<double>() * cuw) * rho;
-                                double s;
-                                if constexpr (!wall_in_fluid_pass<S>()) {
-                                    stb(fpost + (long long)Dir<i, L>::opp * Np, (uint32_t)idx * (uint32_t)sizeof(S),
-                                        pop_put<S>(fr[i] + g, Dir<i, L>::template w<T>(), rown));
-                                    drho += g;
-                                    s = (double)(a[i] + g);
-                                } else {
-                                    s = (double)(a[i] - g);  // 2 (f*_i + g) - g
-                                }
-                                if constexpr (Dir<i, L>::x == 1) fx += s;
-                                if constexpr (Dir<i, L>::x == -1) fx -= s;
-                                if constexpr (Dir<i, L>::y == 1) fy += s;
-                                if constexpr (Dir<i, L>::y == -1) fy -= s;
-                                if constexpr (Dir<i, L>::z == 1) fz += s;
-                                if constexpr (Dir<i, L>::z == -1) fz -= s;
-                            }
-                        }
-                    });
-                    v[0] = fx;
-                    v[1] = fy;
-                    v[2] = fz;
-                    v[3] = ry * fz - rz * fy;
-                    v[4] = rz * fx - rx * fz;
-                    v[5] = rx * fy - ry * fx;
-                } else if (touched & (1u << b)) {
-                    // repulsion between this solid node p of body b1 and the solid nodes q = p + d of
-                    // bodies above b1: on b1 at p (b == b1), or the reaction on b at q (b != b1).  With
-                    // r the offset of p from the centre of b, the torque is r x (sum f) for b1 and
-                    // r x (sum f) + sum d x f for the reaction, so each pair costs a few additions.
-                    const bool react = b != b1;
-                    double sfx = 0.0, sfy = 0.0, sfz = 0.0, tdx = 0.0, tdy = 0.0, tdz = 0.0;
-                    if (b == b1) {
-                        sfx = rsum[wave][0][lane];
-                        sfy = rsum[wave][1][lane];
-                        sfz = rsum[wave][2][lane];
-                    } else if (b == rb2) {
-                        sfx = rsum[wave][3][lane];
-                        sfy = rsum[wave][4][lane];
-                        sfz = rsum[wave][5][lane];
-                        tdx = rsum[wave][6][lane];
-                        tdy = rsum[wave][7][lane];
-                        tdz = rsum[wave][8][lane];
-                    }
-                    // the reaction on a further body (rare): a pass of its own
-                    const int nrep = react && b != rb2 && rmulti ? st->n_rep : 0;
-                    for (int j0 = 0; j0 < nrep; j0 += RC) {
-                        cell_t mqs[RC];
+                    const double *BV = bt[b] + 3, *BW = BV + 3;
+                    double r[3];
+                    lever(b, c, r);
+                    const double u0x = BV[0] + (BW[1] * r[2] - BW[2] * r[1]), u0y = BV[1] + (BW[2] * r[0] - BW[0] * r[2]),
+                                 u0z = BV[2] + (BW[0] * r[1] - BW[1] * r[0]);
 #pragma unroll
-                        for (int j = 0; j < RC; ++j) {
-                            const int o = st->rep_off[j0 + j < nrep ? j0 + j : j0];
-                            const int dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
-                            mqs[j] = mask[wrapi(x + dx, nx) + nx * (wrapi(y + dy, ny) + ny * wrapi(z + dz, nz))];
-                        }
-#pragma unroll
-                        for (int j = 0; j < RC; ++j) {
-                            if (j0 + j >= nrep) break;
-                            const cell_t mq = mqs[j];
-                            if (!(mq & C_SOLID)) continue;
-                            const int b2 = owner_of(mq);
-                            if (b2 <= b1 || (react && b != b2)) continue;
-                            // force on b1 at p, directed from q to p; its opposite on b2 at q
-                            const double sg = react ? -1.0 : 1.0;
-                            const double fx = sg * st->rep_f[j0 + j][0], fy = sg * st->rep_f[j0 + j][1],
-                                         fz = sg * st->rep_f[j0 + j][2];
-                            sfx += fx;
-                            sfy += fy;
-                            sfz += fz;
-                            if (react) {
-                                const int o = st->rep_off[j0 + j];
-                                const double dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
-                                tdx += dy * fz - dz * fy;
-                                tdy += dz * fx - dx * fz;
-                                tdz += dx * fy - dy * fx;
+                    for (int k = 0; k < NS; ++k) {
+                        if (own[k] == b) {
+                            const int i = 1 + q + 8 * k, opp = (i & 1) ? i + 1 : i - 1;
+                            const double dx = dir_rt(i, 0), dy = dir_rt(i, 1), dz = dir_rt(i, 2);
+                            const int c2 = i <= 6 ? 1 : (i <= 18 ? 2 : 3);
+                            const double w = c2 == 1 ? L::wshell[1] : (c2 == 2 ? L::wshell[2] : L::wshell[3]);
+                            const double cuw = dx * u0x + dy * u0y + dz * u0z;
+                            // moving-wall term g: the reflected population becomes f*_i + g (Sec.
+                            // 3.2.2); the link carries 2 f*_i + g to the body plus the
+                            // pseudopotential reaction, both along c_i
+                            const T gr = T(-6.0 * w * cuw), g = gr * rho;
+                            double s;
+                            if constexpr (!wall_in_fluid_pass<S>()) {
+                                stb(fpost + (long long)opp * Np, is, pop_put<S>(fr[k] + g, (T)w, rown));
+                                gs[k] = gr;
+                                s = (double)(a[k] + g);
+                            } else {
+                                s = (double)(a[k] - g);  // 2 (f*_i + g) - g
                             }
+                            v[0] += dx * s;
+                            v[1] += dy * s;
+                            v[2] += dz * s;
                         }
                     }
-                    const double *BX = bt[wave][b];
-                    const double rx = mimg(x - BX[0], nx), ry = mimg(y - BX[1], ny), rz = mimg(z - BX[2], nz);
-                    v[0] = sfx;
-                    v[1] = sfy;
-                    v[2] = sfz;
-                    v[3] = ry * sfz - rz * sfy + tdx;
-                    v[4] = rz * sfx - rx * sfz + tdy;
-                    v[5] = rx * sfy - ry * sfx + tdz;
+                    v[3] = r[1] * v[2] - r[2] * v[1];
+                    v[4] = r[2] * v[0] - r[0] * v[2];
+                    v[5] = r[0] * v[1] - r[1] * v[0];
                 }
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    const double s = wave_sum(v[c]);
-                    if (lane == 0) acc[wave][b][c] += s;
-                }
+                add(b, v);
+                if constexpr (!wall_in_fluid_pass<S>()) drho = ordered_sum<L::Q>(drho, gs, rho);
             }
-            if (!wall_in_fluid_pass<S>() && fluid && nbits) {
-                // the rest population gives back the moving-wall terms (mass correction, Sec. 3.2.2)
-                const uint32_t is = (uint32_t)idx * (uint32_t)sizeof(S);
-                const T f0 = pop_get<S>(ldb(fpost, is), Dir<0, L>::template w<T>(), rown);
-                stb(fpost, is, pop_put<S>(f0 - drho, Dir<0, L>::template w<T>(), rown));
+            // the rest population gives back the moving-wall terms (mass correction, Sec. 3.2.2)
+            if constexpr (!wall_in_fluid_pass<S>())
+                if (has && q == 0) stb(fpost, is, pop_put<S>(f0 - drho, Dir<0, L>::template w<T>(), rown));
+        }
+        // Repulsion between a solid node p of body b1 and the solid nodes q = p + d of bodies above
+        // b1: the force on b1 at p, its opposite on b2 at q.  The n_rep offsets lie across the lanes
+        // (at most four rounds; two for r_c = 3), PN nodes at a time; the sums run per body b2 met.
+        // With r the offset of p from a centre, the torque of the reaction is r x (-s) - sum d x f.
+        constexpr int PN = 4;
+        for (int j0 = 0; j0 < nrepc; j0 += PN) {
+            int c[PN][3], b1[PN];  // the nodes of the batch, the same in every lane
+#pragma unroll
+            for (int j = 0; j < PN; ++j) {
+                int u[3], cv[3];
+                it.cell(keep[wave][CAP - 1 - (j0 + j < nrepc ? j0 + j : j0)], u, cv);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) c[j][k] = __builtin_amdgcn_readfirstlane(cv[k]);
+                b1[j] = j0 + j < nrepc ? __builtin_amdgcn_readfirstlane(owner_of(mask[c[j][0] + nx * (c[j][1] + ny * c[j][2])]))
+                                       : PF_LBM_MAX_BODIES;
+            }
+            const int nrep = st->n_rep;
+            for (int o0 = 0; o0 < nrep; o0 += 64) {
+                const bool on = o0 + lane < nrep;
+                const int o = st->rep_off[on ? o0 + lane : 0];
+                const int dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
+                cell_t mq[PN];
+#pragma unroll
+                for (int j = 0; j < PN; ++j)
+                    mq[j] = mask[wrapl(c[j][0] + dx, nx) + nx * (wrapl(c[j][1] + dy, ny) + ny * wrapl(c[j][2] + dz, nz))];
+#pragma unroll 1
+                for (int j = 0; j < PN; ++j) {
+                    const cell_t m = j == 0 ? mq[0] : (j == 1 ? mq[1] : (j == 2 ? mq[2] : mq[3]));
+                    const int bj = j == 0 ? b1[0] : (j == 1 ? b1[1] : (j == 2 ? b1[2] : b1[3]));
+                    const int b2 = on && (m & C_SOLID) ? owner_of(m) : -1;
+                    uint64_t hits = __ballot(b2 > bj);
+                    if (!hits) continue;
+                    int cj[3];
+                    for (int k = 0; k < 3; ++k) cj[k] = j == 0 ? c[0][k] : (j == 1 ? c[1][k] : (j == 2 ? c[2][k] : c[3][k]));
+                    double fx = 0.0, fy = 0.0, fz = 0.0;
+                    if (on) {
+                        fx = st->rep_f[o0 + lane][0];
+                        fy = st->rep_f[o0 + lane][1];
+                        fz = st->rep_f[o0 + lane][2];
+                    }
+                    while (hits) {
+                        const int bb = __shfl(b2, (int)__builtin_ctzll(hits), 64);
+                        const bool mine = b2 == bb;
+                        hits &= ~__ballot(mine);
+                        const double v[6] = {mine ? fx : 0.0,
+                                             mine ? fy : 0.0,
+                                             mine ? fz : 0.0,
+                                             mine ? dy * fz - dz * fy : 0.0,
+                                             mine ? dz * fx - dx * fz : 0.0,
+                                             mine ? dx * fy - dy * fx : 0.0};
+                        const double tot = wave_sum6(v);
+                        double s[3], td[3], r1[3], r2[3];
+                        for (int k = 0; k < 3; ++k) {
+                            s[k] = __shfl(tot, 8 * k, 64);
+                            td[k] = __shfl(tot, 8 * (3 + k), 64);
+                        }
+                        lever(bj, cj, r1);
+                        lever(bb, cj, r2);
+                        if (lane == 0) {
+                            double *A = acc[wave][bj], *R = acc[wave][bb];
+                            for (int k = 0; k < 3; ++k) {
+                                const int m1 = (k + 1) % 3, m2 = (k + 2) % 3;
+                                A[k] += s[k];
+                                A[3 + k] += r1[m1] * s[m2] - r1[m2] * s[m1];
+                                R[k] -= s[k];
+                                R[3 + k] -= r2[m1] * s[m2] - r2[m2] * s[m1] + td[k];
+                            }
+                        }
+                    }
+                }
             }
         }
         __builtin_amdgcn_wave_barrier();

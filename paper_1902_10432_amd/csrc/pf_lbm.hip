@@ -299,7 +299,7 @@ int default_tz(int nx, int ny, int nz, int ty) {
 }
 
 template <typename S, class Lat, int TY>
-void launch_fluid_ty(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S> *psi, const ArT<S> *psi_prev,
+void launch_fluid_ty(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S> *psi, ArT<S> *psi_prev,
                      const cell_t *mask, BodyDev *cur, int par, StepState *st, const ClassifyPart *cpart,
                      const uint32_t *nbw) {
     if constexpr (fluid_tile_fits<S, Lat, TY>()) {
@@ -312,7 +312,7 @@ void launch_fluid_ty(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S>
 }
 
 template <typename S, class Lat>
-void launch_fluid(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S> *psi, const ArT<S> *psi_prev,
+void launch_fluid(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S> *psi, ArT<S> *psi_prev,
                   const cell_t *mask, BodyDev *cur, int par, StepState *st, const ClassifyPart *cpart,
                   const uint32_t *nbw) {
     if (h->fluid_ty == 16)
@@ -419,7 +419,7 @@ int enqueue_step(pf_lbm *h, double *parts = nullptr) {
         const int fbk = h->force_grid;
         uint4 *tstate = (uint4 *)(h->ws + h->L.tstate);
         uint32_t *thot = (uint32_t *)(h->ws + h->L.thot), *tact = (uint32_t *)(h->ws + h->L.tact);
-        k_body_forces<S, Lat><<<dim3(fbk), dim3(64 * force_waves<T, Lat>()), 0, s>>>(p, par, st, fc, fn, psi, psi_prev,
+        k_body_forces<S, Lat><<<dim3(fbk), dim3(64 * FORCE_WAVES), 0, s>>>(p, par, st, fc, fn, psi, psi_prev,
                                                                                       mask, cur, pforce, nbw);
         // tile activity, and in its last block the rigid-body update from the force partials
         k_tile_activity<T><<<dim3(std::min(h->box_grid, 64) + 1), b, 0, s>>>(
