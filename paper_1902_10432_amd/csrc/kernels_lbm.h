@@ -311,6 +311,12 @@ template <int TY>
 struct FluidShape {
     static constexpr int W = TY <= 4 ? 4 : 8, RPT = TY / W;
 };
+// waves per SIMD that the registers have to allow: four where two 8-wave blocks fit a CU by their LDS
+// and the register count would otherwise end just above 128
+template <typename S, class L, int TY>
+constexpr int fluid_min_waves() {
+    return L::Q == 27 && sizeof(S) == 4 && TY == 8 ? 4 : 1;
+}
 constexpr size_t FLUID_LDS_MAX = 80 * 1024;
 template <typename S, class L, int TY>
 constexpr bool fluid_tile_fits() {
@@ -355,11 +361,12 @@ __device__ __forceinline__ ArT<S> node_psi_of(const Prm<ArT<S>> &p, const BodyDe
 // pass they have landed, psi of plane z + 2 is formed, and so on.  Instantiations whose halo
 // buffers do not fit the LDS budget load the halo of each plane just before its psi is formed.
 //
-// With bodies, the first block also publishes the step's box, solid radii, volume terms and event
-// flag from the previous reclassification (publish_step_state) before its own cells: that short
-// reduction chain then hides behind the longest pass of the step instead of costing a launch.
+// With bodies, block 0 is an extra one that only publishes the step's box, solid radii, volume terms
+// and event flag from the previous reclassification (publish_step_state): that reduction chain runs
+// beside the tiles instead of costing a launch, or, on a small grid where every tile runs at once,
+// instead of delaying the block that would run it first.
 template <typename S, class L, int TY>
-__global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<ArT<S>> p, const S *__restrict__ fin,
+__global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY>())) void k_collide_stream(Prm<ArT<S>> p, const S *__restrict__ fin,
                                                                      S *__restrict__ fout, ArT<S> *__restrict__ psi,
                                                                      ArT<S> *__restrict__ psi_prev,
                                                                      const cell_t *__restrict__ mask, BodyDev *bodies,
@@ -373,8 +380,11 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<A
     __shared__ FluidLds<S, L, TY, DMA> lds;
     constexpr bool H = sizeof(S) == 2;
     const int tid = (int)threadIdx.x, tx = tid & 63, wv = tid >> 6;
-    if (cpart && blockIdx.x == 0)
+    const int extra = cpart ? 1 : 0;
+    if (extra && blockIdx.x == 0) {
         publish_step_state(wv, W, parity, p.nx, p.ny, p.nz, p.nb, p.eta, st, bodies, cpart, cblk);
+        return;
+    }
     // FP16 form: the bodies' motion for the moving-wall term into LDS (ordered before its first
     // use by the prologue's barrier)
     if constexpr (wall_in_fluid_pass<S>()) {
@@ -396,7 +406,7 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W) void k_collide_stream(Prm<A
     };
     const int nx = p.nx, ny = p.ny, nz = p.nz;
     const int tiles_x = (nx + 63) / 64, tiles_y = (ny + TY - 1) / TY, tiles = tiles_x * tiles_y;
-    const int b = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int b = xcd_block((int)blockIdx.x - extra, (int)gridDim.x - extra);
     const int chunk = b / tiles, tile = b - chunk * tiles;
     const int tyi = tile / tiles_x, txi = tile - tyi * tiles_x;
     const int x0 = txi * 64, y0 = tyi * TY, zs = chunk * tz, ze = min(zs + tz, nz);

@@ -289,13 +289,40 @@ bool fluid_ty_ok(int ty) {
 }
 
 
-// planes per z-chunk: the longest power of two in [4, 64] that still gives the grid 1024 blocks
-// (four per CU), 4 when none does
-int default_tz(int nx, int ny, int nz, int ty) {
-    const long long tiles = (long long)((nx + 63) / 64) * ((ny + ty - 1) / ty);
-    int tz = 64;
-    while (tz > 4 && tiles * ((nz + tz - 1) / tz) < 1024) tz /= 2;
-    return tz;
+// Default tile rows of the fluid pass: 8, and 4 where a block of 8 waves would hold a CU alone
+// (FP64: LDS; FP16 storage: registers, three 4-wave blocks per CU against one of 8 waves; 256^3 four
+// spheres, FP16: 744 us a step with 4 rows, 862 with 8, 864 with 16).
+int default_ty(int prec) { return prec == PF_LBM_FP32 ? 8 : 4; }
+
+// Default planes per z-chunk.  A block's time is about tz + 1.5 planes (two more planes of psi), and
+// the card holds 256 * per_cu blocks at once, so the chunk is the one of least rounds * (tz + 1.5),
+// with half a round for the tail where there is more than one: on small grids short chunks that
+// give every CU a block (61 x 45 x 50, FP32: 72 us a step with one plane, 83 with 4, 99 with 8), at
+// 128^3 the one round of 8 planes (171 us; 4: 176, 2: 188).  Large grids run at the memory rate, flat
+// between 8 and 16 planes (256^3 FP32: 4: 1032, 8: 962, 16: 967, 32: 989 us a step), and FP16 storage
+// loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).
+int default_tz(int nx, int ny, int nz, int ty, int per_cu) {
+    const double tiles = (double)((nx + 63) / 64) * ((ny + ty - 1) / ty), slots = 256.0 * per_cu;
+    auto cost = [&](int tz) {
+        const double r = tiles * ((nz + tz - 1) / tz) / slots;
+        return (r <= 1.0 ? 1.0 : r + 0.5) * (tz + 1.5);
+    };
+    int best = 1;
+    for (int tz : {2, 3, 4, 6, 8})
+        if (cost(tz) < cost(best)) best = tz;
+    return best;
+}
+
+// blocks of the default fluid-pass tile that a CU holds at once (LDS and registers)
+template <typename S, class Lat, int TY>
+int fluid_per_cu() {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)k_collide_stream<S, Lat, TY>,
+                                                     64 * FluidShape<TY>::W, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        n = 2;
+    }
+    return std::max(n, 1);
 }
 
 template <typename S, class Lat, int TY>
@@ -306,7 +333,7 @@ void launch_fluid_ty(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S>
         const int tz = h->fluid_tz;
         const unsigned tiles = (unsigned)(((h->cfg.nx + 63) / 64) * ((h->cfg.ny + TY - 1) / TY));
         const unsigned chunks = (unsigned)((h->cfg.nz + tz - 1) / tz);
-        k_collide_stream<S, Lat, TY><<<dim3(tiles * chunks), dim3(64 * FluidShape<TY>::W), 0, h->stream>>>(
+        k_collide_stream<S, Lat, TY><<<dim3(tiles * chunks + (cpart ? 1 : 0)), dim3(64 * FluidShape<TY>::W), 0, h->stream>>>(
             p, fc, fn, psi, psi_prev, mask, cur, par, st, cpart, h->cgrid, nbw, tz);
     }
 }
@@ -618,8 +645,14 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
     h->box_grid = box_grid;
     h->force_grid = force_grid;
     h->cgrid = cgrid;
-    h->fluid_ty = cfg->precision == PF_LBM_FP64 ? 4 : 8;
-    h->fluid_tz = default_tz(cfg->nx, cfg->ny, cfg->nz, h->fluid_ty);
+    h->fluid_ty = default_ty(cfg->precision);
+    const int per_cu = h->q == 27 ? (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q27, 4>()
+                                     : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q27, 8>()
+                                                              : fluid_per_cu<half_t, D3Q27, 4>())
+                                  : (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q19, 4>()
+                                     : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q19, 8>()
+                                                              : fluid_per_cu<half_t, D3Q19, 4>());
+    h->fluid_tz = default_tz(cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
     const int np1 = n_bodies + 1;
     h->sigma.assign((size_t)np1 * np1, 0.0);
     for (int a = 0; a < np1; ++a)
