@@ -28,13 +28,25 @@ __device__ __forceinline__ T mc_flux(T u, T am1, T a0, T a1, T a2) {
     return u * (a1 - T(0.5) * (T(1) + u) * mc_slope(a1 - a0, a2 - a1));
 }
 
-// Sum K values of per-block partials part[k * nblk + j] into out[k] with the whole block:
-// wave w takes k = w, w + 4, ...; fixed order (deterministic).
+// Sum K values of per-block partials part[k * nblk + j], nblk <= 256, into out[k] with a block of
+// four waves: wave w takes k = w, w + 4, ..., the loads of four of them in one round; fixed order
+// (deterministic).
 __device__ __forceinline__ void block_totals(const double *part, int nblk, int K, double *out) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int k = wave; k < K; k += 4) {
-        const double s = wave_sum_array(part + (long long)k * nblk, nblk);
-        if (lane == 0) out[k] = s;
+    for (int k0 = wave; k0 < K; k0 += 16) {
+        double v[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool on = k0 + 4 * g < K && lane + 64 * j < nblk;
+                v[g][j] = on ? part[(long long)(k0 + 4 * g) * nblk + lane + 64 * j] : 0.0;
+            }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const double s = wave_sum((v[g][0] + v[g][1]) + (v[g][2] + v[g][3]));
+            if (lane == 0 && k0 + 4 * g < K) out[k0 + 4 * g] = s;
+        }
     }
     __syncthreads();
 }
@@ -481,9 +493,12 @@ __device__ __forceinline__ void rigid_body_update(int flags, int nbod, StepState
                                                   int fblk, double *__restrict__ hist, int hcap) {
     __shared__ double tot[PF_LBM_MAX_BODIES * 6];
     const int tid = threadIdx.x;
+    // the table entry is read beside the partials, not after their sums
+    BodyDev B;
+    if (tid < nbod) B = cur[tid];
+    const uint32_t step = st->step_no;
     block_totals(fpart, fblk, nbod * 6, tot);
     if (tid < nbod) {
-        const BodyDev &B = cur[tid];
         const double *F = &tot[tid * 6], *Tq = &tot[tid * 6 + 3];
         BodyDev Bn = B;
         bool finite = true;
@@ -502,7 +517,7 @@ __device__ __forceinline__ void rigid_body_update(int flags, int nbod, StepState
         next[tid] = Bn;
         if (!finite) atomicOr(&st->err, 1u);
         if (hist) {
-            double *hrow = hist + ((long long)((st->step_no - 1u) % (uint32_t)hcap) * nbod + tid) * 6;
+            double *hrow = hist + ((long long)((step - 1u) % (uint32_t)hcap) * nbod + tid) * 6;
             for (int d = 0; d < 3; ++d) {
                 hrow[d] = F[d];
                 hrow[3 + d] = Tq[d];
@@ -543,37 +558,38 @@ __global__ __launch_bounds__(256) void k_tile_activity(Prm<T> p, int parity, Ste
         t -= t >= n ? n : 0;
         return t;
     };
-    const bool near = p.trad[0] == 1 && p.trad[1] == 1 && p.trad[2] == 1;
+    // an x-y slice of the neighbourhood per round of loads (9 words; 25 where an axis reaches two
+    // tiles): loops over single words would wait for memory once per word
+    const bool near = p.trad[0] == 1 && p.trad[1] == 1;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < ti.total; k += nblk * 256) {
         int tc[3];
         const int tl = ti.tile(k, tc);
+        const uint32_t s0 = word(tl);
         uint32_t dif = 0;
-        if (near) {
-            // the 27 words in one round of loads
-            int xs[3], ys[3], zs[3];
+        auto slice = [&](auto RR, int z) {
+            constexpr int R = decltype(RR)::value, E = 2 * R + 1;
+            int xs[E], ys[E];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                xs[d] = wrapt(tc[0] + d - 1, p.tn[0]);
-                ys[d] = p.tn[0] * wrapt(tc[1] + d - 1, p.tn[1]);
-                zs[d] = p.tn[0] * p.tn[1] * wrapt(tc[2] + d - 1, p.tn[2]);
+            for (int d = 0; d < E; ++d) {
+                xs[d] = wrapt(tc[0] + max(-p.trad[0], min(p.trad[0], d - R)), p.tn[0]);
+                ys[d] = p.tn[0] * (wrapt(tc[1] + max(-p.trad[1], min(p.trad[1], d - R)), p.tn[1]) + p.tn[1] * z);
             }
-            uint32_t w[27];
+            uint32_t w[E * E];
 #pragma unroll
-            for (int j = 0; j < 27; ++j) w[j] = word(xs[j % 3] + ys[(j / 3) % 3] + zs[j / 9]);
-            const uint32_t s0 = w[13];
+            for (int j = 0; j < E * E; ++j) w[j] = word(xs[j % E] + ys[j / E]);
 #pragma unroll
-            for (int j = 0; j < 27; ++j) dif |= (w[j] ^ s0) | (w[j] & (w[j] >> 1) & PAIR_LO);
+            for (int j = 0; j < E * E; ++j) dif |= (w[j] ^ s0) | (w[j] & (w[j] >> 1) & PAIR_LO);
+        };
+        if (near && p.trad[2] == 1) {
+#pragma unroll
+            for (int dz = -1; dz <= 1; ++dz) slice(std::integral_constant<int, 1>{}, wrapt(tc[2] + dz, p.tn[2]));
         } else {
-            const uint32_t s0 = word(tl);
             for (int dz = -p.trad[2]; dz <= p.trad[2]; ++dz) {
                 const int z = wrapt(tc[2] + dz, p.tn[2]);
-                for (int dy = -p.trad[1]; dy <= p.trad[1]; ++dy) {
-                    const int y = wrapt(tc[1] + dy, p.tn[1]);
-                    for (int dx = -p.trad[0]; dx <= p.trad[0]; ++dx) {
-                        const uint32_t s = word(wrapt(tc[0] + dx, p.tn[0]) + p.tn[0] * (y + p.tn[1] * z));
-                        dif |= (s ^ s0) | (s & (s >> 1) & PAIR_LO);
-                    }
-                }
+                if (near)
+                    slice(std::integral_constant<int, 1>{}, z);
+                else
+                    slice(std::integral_constant<int, 2>{}, z);
             }
         }
         const uint32_t hot = (dif | (dif >> 1)) & pm;
