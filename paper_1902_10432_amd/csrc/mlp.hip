@@ -205,6 +205,8 @@ struct TrainBuf {
 // four products).  The first layer takes the FP32 inputs rounded to BF16 (K padded with zeros to 32);
 // the output layer is a dot product of each row with the output weights in a fixed order.
 //
+// Inference can take its row count from the device (n_dev, at most M); blocks past it return.
+//
 // What bounds it: the SiLU of every hidden unit on large batches (the exponential and the division
 // take more issue slots than the matrix instructions), the layers' latencies on small ones.
 // 4 -> 128 x 4 -> 1: gradients of 8192 rows 8997 -> 130 us a call and a training step of 205 rows
@@ -213,7 +215,8 @@ struct TrainBuf {
 template <int H, int RS, bool TRAIN>
 __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, int M, int nin, LayerMap lm,
                                                    const __bf16 *__restrict__ Wb, const __bf16 *__restrict__ Wt,
-                                                   const float *__restrict__ P, float *__restrict__ y, TrainBuf tb) {
+                                                   const float *__restrict__ P, float *__restrict__ y, TrainBuf tb,
+                                                   const int *__restrict__ n_dev) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     constexpr int NT = H / 64, KS = H / 32, LD = H + 8, ROWS = 16 * RS;
     __shared__ __attribute__((aligned(16))) __bf16 act[2][ROWS][LD];
@@ -222,6 +225,10 @@ __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int rl = lane & 15, kq = 8 * (lane >> 4), fq = 4 * (lane >> 4);
     const int r0 = blockIdx.x * ROWS;
+    if constexpr (!TRAIN) {
+        if (n_dev) M = min(M, *n_dev);
+        if (r0 >= M) return;  // whole block
+    }
     const int L = lm.n - 1;
     auto feat = [&](int t) { return 16 * (wave * NT + t); };  // first column of this wave's tile t
     // this wave's slice of a square layer's weights, row-major [H][H]
@@ -815,28 +822,28 @@ void run_backward(pf_mlp *h, const float *t, int n, int chunks, int chunk) {
 int fused_rows(int n) { return n > 16 * 512 ? 64 : 16; }
 
 template <int H, bool TRAIN>
-void launch_fused(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb) {
+void launch_fused(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb, const int *n_dev) {
     const int rows = fused_rows(n);
     const unsigned g = (unsigned)((n + rows - 1) / rows);
     if (rows == 64)
         k_mlp_fused<H, 4, TRAIN><<<g, 256, 0, h->stream>>>(x, n, h->cfg.n_in, h->lm, at<__bf16>(h, h->Wb),
-                                                           at<__bf16>(h, h->Wt), at<float>(h, h->P), y, tb);
+                                                           at<__bf16>(h, h->Wt), at<float>(h, h->P), y, tb, n_dev);
     else
         k_mlp_fused<H, 1, TRAIN><<<g, 256, 0, h->stream>>>(x, n, h->cfg.n_in, h->lm, at<__bf16>(h, h->Wb),
-                                                           at<__bf16>(h, h->Wt), at<float>(h, h->P), y, tb);
+                                                           at<__bf16>(h, h->Wt), at<float>(h, h->P), y, tb, n_dev);
 }
 
 // the one-launch network passes exist for these widths; others run layer by layer
 bool fused_width(int H) { return H == 64 || H == 128 || H == 256; }
 
 template <bool TRAIN>
-void launch_fused_any(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb) {
+void launch_fused_any(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb, const int *n_dev = nullptr) {
     if (h->cfg.hidden == 64)
-        launch_fused<64, TRAIN>(h, x, n, y, tb);
+        launch_fused<64, TRAIN>(h, x, n, y, tb, n_dev);
     else if (h->cfg.hidden == 128)
-        launch_fused<128, TRAIN>(h, x, n, y, tb);
+        launch_fused<128, TRAIN>(h, x, n, y, tb, n_dev);
     else
-        launch_fused<256, TRAIN>(h, x, n, y, tb);
+        launch_fused<256, TRAIN>(h, x, n, y, tb, n_dev);
 }
 
 // loss, parameter gradients into G and with lr > 0 the Adam step
@@ -907,6 +914,13 @@ __attribute__((visibility("hidden"))) void pfm_internal_info(const pf_mlp *h, in
     *n_in = h ? h->cfg.n_in : 0;
     *max_batch = h ? h->cfg.max_batch : 0;
     *stream = h ? (void *)h->stream : nullptr;
+}
+
+__attribute__((visibility("hidden"))) bool pfm_internal_forward_counted(pf_mlp *h, const float *x, int max_rows,
+                                                                        const int *n_dev, float *y) {
+    if (!fused_width(h->cfg.hidden)) return false;
+    launch_fused_any<false>(h, x, max_rows, y, TrainBuf{}, n_dev);
+    return true;
 }
 
 extern "C" {
