@@ -56,7 +56,7 @@ __device__ __forceinline__ void sfor(F &&f) {
 
 // ---- cell word (one uint32 per node): bit 31 solid, bit 30 became solid this step, bit 29
 // became fluid this step, bits 24-28 owning body of a solid node, bit i (1..18) set when the
-// neighbour in direction i is solid (D3Q19 only; kept current inside the body box by k_post)
+// neighbour in direction i is solid (D3Q19 only; kept current by k_convert)
 using cell_t = uint32_t;
 constexpr uint32_t C_SOLID = 1u << 31, C_F2S = 1u << 30, C_S2F = 1u << 29, C_NBMASK = 0x7FFFEu;
 __device__ __forceinline__ int owner_of(uint32_t w) { return (int)((w >> 24) & 31u); }

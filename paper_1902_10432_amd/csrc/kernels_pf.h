@@ -802,7 +802,7 @@ struct Nbhd {
 // Node conversion at one fluid node r (Sec. 3.2.2): the node gathers, from each neighbour that
 // just became solid and whose neighbourhood N_F contains it, f_eq(rho_n, u_n) / |N_F| with
 // rho_n, u_n = j_n / rho_n of the converted node's populations; a node that just became fluid
-// starts from empty populations.  Sources are only read here (k_post empties them).
+// starts from empty populations.  Sources are only read.
 // psi: the pseudopotential of this step (reference density of the FP16 form)
 template <typename S, class L>
 __device__ void gather_receiver(const Prm<ArT<S>> &p, const cell_t *__restrict__ mask, S *f,
@@ -857,17 +857,50 @@ __device__ void gather_receiver(const Prm<ArT<S>> &p, const cell_t *__restrict__
 }
 
 
-// Node conversion, receiving side, after the reclassification of the step.  Usual case: no node
-// changed side and the kernel returns at once.  Otherwise the event list drives it: work item
-// (event e, neighbour d) handles the fluid node r = e + d when e is the converted node of lowest
-// index among r's neighbours (so each receiver is handled once, in a fixed order of its sources),
-// and a node that became fluid with no converted neighbour is emptied.  When the list overflowed,
-// the whole box is scanned instead.
+// Neighbour bits of one node (bit i: the node in direction i is solid) from the words of its
+// neighbours: D3Q19 in its cell word, D3Q27 in its neighbour-bit word.  Only solid bits of neighbours
+// are read, which this never changes, so repeated visits of one node write the same word.
+template <class L>
+__device__ __forceinline__ void refresh_bits(int nx, int ny, int nz, cell_t *mask, uint32_t *nbw, int x, int y, int z,
+                                             uint32_t idx) {
+    const cell_t m = mask[idx];
+    uint32_t bits = 0;
+    // the neighbours' words in rounds of nine loads (one latency per round, few registers)
+    const Nbr nb(x, y, z, nx, ny, nz);
+#pragma unroll 1
+    for (int i0 = 1; i0 < L::Q; i0 += 9) {
+        cell_t w[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int i = i0 + j < L::Q ? i0 + j : 0;  // direction 0: the node itself, ignored
+            w[j] = mask[(int)idx + nb.off_rt(i)];
+        }
+#pragma unroll
+        for (int j = 0; j < 9; ++j)
+            if (i0 + j < L::Q && (w[j] & C_SOLID)) bits |= 1u << (i0 + j);
+    }
+    const cell_t mn = (m & ~C_NBMASK) | (L::kBits ? bits : 0u);
+    if (mn != m) mask[idx] = mn;
+    if constexpr (!L::kBits)
+        if (nbw[idx] != bits) nbw[idx] = bits;
+}
+
+// Node conversion after the reclassification of the step, receivers and neighbour bits.  Usual case:
+// no node changed side and the kernel returns at once.  Otherwise the event list drives it:
+//  * work item (event e, neighbour d) handles the fluid node r = e + d when e is the converted node of
+//    lowest index among r's neighbours (so each receiver is handled once, in a fixed order of its
+//    sources), and a node that became fluid with no converted neighbour is emptied;
+//  * work item (event e, direction i) refreshes the neighbour bits of the node that has e as its
+//    neighbour in direction i (and of e itself), for the next step's fluid pass.
+// When the list overflowed, the whole box is scanned instead.  The two kinds of item run side by
+// side: a receiver reads the solid bits and event marks of words, which a refresh keeps.  The marks
+// stay until the next reclassification, which visits every node that changed side (its tile is
+// mixed) and writes its word anew; the populations of a node that became solid stay too, as nothing
+// reads populations of solid nodes (it starts from empty ones when it becomes fluid again).
 template <typename S, class L>
-__global__ __launch_bounds__(256) void k_convert_gather(Prm<ArT<S>> p, int parity, StepState *st,
-                                                        const cell_t *__restrict__ mask, S *f,
-                                                        const ArT<S> *__restrict__ psi,
-                                                        const uint32_t *__restrict__ evlist, uint32_t evcap) {
+__global__ __launch_bounds__(256) void k_convert(Prm<ArT<S>> p, int parity, StepState *st, cell_t *mask, uint32_t *nbw,
+                                                 S *f, const ArT<S> *__restrict__ psi,
+                                                 const uint32_t *__restrict__ evlist, uint32_t evcap) {
     using T = ArT<S>;
     const uint32_t nev = st->n_events;
     if (!nev) return;
@@ -883,6 +916,7 @@ __global__ __launch_bounds__(256) void k_convert_gather(Prm<ArT<S>> p, int parit
             int u[3], c[3];
             it.cell(k, u, c);
             const int idx = c[0] + nx * (c[1] + ny * c[2]);
+            refresh_bits<L>(nx, ny, nz, mask, nbw, c[0], c[1], c[2], (uint32_t)idx);
             const cell_t m = mask[idx];
             if (m & C_F2S) {
                 double r2;
@@ -896,7 +930,17 @@ __global__ __launch_bounds__(256) void k_convert_gather(Prm<ArT<S>> p, int parit
         if (lost) atomicAdd(&st->n_lost, lost);  // rare
         return;
     }
-    for (int j = gtid; j < (int)nev * 27; j += gstride) {
+    const int ngather = (int)nev * 27;
+    for (int j = gtid; j < ngather + (int)nev * L::Q; j += gstride) {
+        if (j >= ngather) {
+            const uint32_t e = evlist[(j - ngather) / L::Q] & 0x7FFFFFFFu;
+            const int i = (j - ngather) % L::Q;
+            const int ex = (int)(e % (uint32_t)nx), ey = (int)((e / (uint32_t)nx) % (uint32_t)ny), ez = (int)(e / ((uint32_t)nx * ny));
+            // node whose neighbour in direction i is e
+            const int x = wrapi(ex - kCX[i], nx), y = wrapi(ey - kCY[i], ny), z = wrapi(ez - kCZ[i], nz);
+            refresh_bits<L>(nx, ny, nz, mask, nbw, x, y, z, (uint32_t)(x + nx * (y + ny * z)));
+            continue;
+        }
         const uint32_t ent = evlist[j / 27];
         const int d = j % 27;  // 13 = the event node itself
         const uint32_t e = ent & 0x7FFFFFFFu;
@@ -926,107 +970,15 @@ __global__ __launch_bounds__(256) void k_convert_gather(Prm<ArT<S>> p, int parit
     if (lost) atomicAdd(&st->n_lost, lost);  // rare
 }
 
-// Upkeep of the cell words at one node: node conversion, source side (Sec. 3.2.2) -- a node that
-// became solid is emptied (its content was handed on, or counted as lost, by k_convert_gather)
-// -- then the neighbour bits (bit i: the node in direction i is solid) are recomputed and the
-// event bits cleared.  Only solid bits of neighbours are read,
-// which this pass never changes, so repeated visits of one node write the same word.
-// empty: 0 never, 1 when the word carries the "became solid" mark (one visit per node), 2 always
-// (the caller knows the node became solid).
-template <typename S, class L>
-__device__ __forceinline__ void refresh_node(const Prm<ArT<S>> &p, cell_t *mask, uint32_t *nbw, S *f, const ArT<S> *psi,
-                                             int x, int y, int z, uint32_t idx, int empty) {
-    using T = ArT<S>;
-    const int nx = p.nx, ny = p.ny, nz = p.nz;
-    // runtime loops: events are rare, and the kernels that run this keep few registers
-    const cell_t m = mask[idx];
-    if (empty == 2 || (empty == 1 && (m & C_F2S))) {
-        const T rr = sizeof(S) == 2 ? ref_density(psi[idx], p.rho0) : T(0);
-#pragma unroll 1
-        for (int i = 0; i < L::Q; ++i) {
-            const int c2 = kCX[i] * kCX[i] + kCY[i] * kCY[i] + kCZ[i] * kCZ[i];
-            f[(long long)i * p.Np + idx] = pop_put<S>(T(0), T(L::wshell[c2]), rr);
-        }
+// Neighbour bits of every box node (initialisation: the first cell words).
+template <class L>
+__global__ __launch_bounds__(256) void k_post(int nx, int ny, int nz, const StepState *st, cell_t *mask, uint32_t *nbw) {
+    const BoxIter it(st->box[0], nx, ny, nz);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < it.vol; k += gridDim.x * 256) {
+        int u[3], c[3];
+        it.cell(k, u, c);
+        refresh_bits<L>(nx, ny, nz, mask, nbw, c[0], c[1], c[2], (uint32_t)(c[0] + nx * (c[1] + ny * c[2])));
     }
-    uint32_t bits = 0;
-    {
-        // the neighbours' words in rounds of nine loads (one latency per round, few registers)
-        const Nbr nb(x, y, z, nx, ny, nz);
-#pragma unroll 1
-        for (int i0 = 1; i0 < L::Q; i0 += 9) {
-            cell_t w[9];
-#pragma unroll
-            for (int j = 0; j < 9; ++j) {
-                const int i = i0 + j < L::Q ? i0 + j : 0;  // direction 0: the node itself, ignored
-                w[j] = mask[(int)idx + nb.off_rt(i)];
-            }
-#pragma unroll
-            for (int j = 0; j < 9; ++j)
-                if (i0 + j < L::Q && (w[j] & C_SOLID)) bits |= 1u << (i0 + j);
-        }
-    }
-    // D3Q19: the bits in the cell word; D3Q27: in the neighbour-bit word
-    const cell_t mn = (m & ~(C_F2S | C_S2F | C_NBMASK)) | (L::kBits ? bits : 0u);
-    if (mn != m) mask[idx] = mn;
-    if constexpr (!L::kBits)
-        if (nbw[idx] != bits) nbw[idx] = bits;
-}
-
-// Closing work of a step's node conversions, run after the conversion gather: with full != 0
-// (initialisation) or an overflowed event list, every node of the box is refreshed; otherwise
-// only the nodes whose words can have changed: each event node (emptied if it became solid) and
-// the Q - 1 nodes that have it as a neighbour.  Threads gtid (of gstride) take the work in turn.
-template <typename S, class L>
-__device__ __forceinline__ void post_events(const Prm<ArT<S>> &p, const int32_t *box, uint32_t nev,
-                                            cell_t *mask, uint32_t *nbw, S *f, const ArT<S> *psi,
-                                            const uint32_t *evlist, uint32_t evcap, int full, int gtid,
-                                            int gstride) {
-    const int nx = p.nx, ny = p.ny, nz = p.nz;
-    if (full || nev > evcap) {
-        const BoxIter it(box, nx, ny, nz);
-        for (int k = gtid; k < it.vol; k += gstride) {
-            int u[3], c[3];
-            it.cell(k, u, c);
-            refresh_node<S, L>(p, mask, nbw, f, psi, c[0], c[1], c[2], (uint32_t)(c[0] + nx * (c[1] + ny * c[2])),
-                               full ? 0 : 1);
-        }
-    } else {
-        // the event node and the Q - 1 nodes whose bit for it may change
-        constexpr int NR = L::Q;
-        for (int j = gtid; j < (int)nev * NR; j += gstride) {
-            const uint32_t ent = evlist[j / NR];
-            const int i = j % NR;
-            const uint32_t e = ent & 0x7FFFFFFFu;
-            const int ex = (int)(e % (uint32_t)nx), ey = (int)((e / (uint32_t)nx) % (uint32_t)ny), ez = (int)(e / ((uint32_t)nx * ny));
-            // node whose neighbour in direction i is e
-            const int x = wrapi(ex - kCX[i], nx), y = wrapi(ey - kCY[i], ny), z = wrapi(ez - kCZ[i], nz);
-            refresh_node<S, L>(p, mask, nbw, f, psi, x, y, z, (uint32_t)(x + nx * (y + ny * z)),
-                               (i == 0 && (ent & 0x80000000u)) ? 2 : 0);
-        }
-    }
-}
-
-// Every box node refreshed (initialisation: neighbour bits of the first cell words).
-template <typename S, class L>
-__global__ __launch_bounds__(256) void k_post(Prm<ArT<S>> p, int parity, StepState *st, cell_t *__restrict__ mask,
-                                              uint32_t *nbw, S *f, const ArT<S> *__restrict__ psi) {
-    post_events<S, L>(p, st->box[parity], 0u, mask, nbw, f, psi, nullptr, 0u, 1, blockIdx.x * 256 + threadIdx.x,
-                      gridDim.x * 256);
-}
-
-// Closing work of a step's node conversions, launched after the conversion gather (post_events
-// on the step's event list and box): nodes that became solid are emptied (their content was
-// handed on by the gather) and the neighbour bits around every event are refreshed, before the
-// next step's fluid pass reads them.  Usual case: no node changed side and every thread returns
-// at once.  psi: the pseudopotential of this step (reference density of the FP16 form).
-template <typename S, class L>
-__global__ __launch_bounds__(256) void k_close_events(Prm<ArT<S>> p, int parity, StepState *st, S *f, cell_t *mask,
-                                                      uint32_t *nbw, const ArT<S> *__restrict__ psi,
-                                                      const uint32_t *__restrict__ evlist, uint32_t evcap) {
-    const uint32_t nev = st->n_events;
-    if (!nev) return;
-    post_events<S, L>(p, st->box[parity], nev, mask, nbw, f, psi, evlist, evcap, 0, blockIdx.x * 256 + threadIdx.x,
-                      gridDim.x * 256);
 }
 
 // ---- initialisation and read-out helpers ------------------------------------------------------

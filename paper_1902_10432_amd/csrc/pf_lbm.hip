@@ -23,8 +23,8 @@ namespace {
 thread_local std::string g_init_error;
 
 constexpr size_t ALIGN = 256;
-// capacity of the per-step list of nodes that changed side (beyond it the closing kernels scan
-// the whole box)
+// capacity of the per-step list of nodes that changed side (beyond it the conversion scans the
+// whole box)
 constexpr uint32_t EV_CAP = 1u << 16;
 // steps of per-body force / torque history kept on the device (ring)
 constexpr int HIST_CAP = 8192;
@@ -454,11 +454,8 @@ int enqueue_step(pf_lbm *h, double *parts = nullptr) {
         // one kernel per sweep; the phase fields end in buffer A every step
         launch_advect<T>(h, p, par, st, next, phiA, phiB, tact);
         launch_phase_update<T>(h, p, par, st, next, sigma, phiB, phiA, mask, cpart, evlist, tact, tstate);
-        // conversion gather, then its closing pass: both usually return at once (no node changed
-        // side), so a small grid
-        const dim3 ge(std::min(h->box_grid, 64));
-        k_convert_gather<S, Lat><<<ge, b, 0, s>>>(p, par, st, mask, fn, psi, evlist, h->ev_cap);
-        k_close_events<S, Lat><<<ge, b, 0, s>>>(p, par, st, fn, mask, nbw, psi, evlist, h->ev_cap);
+        // conversion: usually returns at once (no node changed side), so a small grid
+        k_convert<S, Lat><<<dim3(std::min(h->box_grid, 64)), b, 0, s>>>(p, par, st, mask, nbw, fn, psi, evlist, h->ev_cap);
     }
     if (ev) HIPCHK(h, hipEventRecord(ev[3], s));
     HIPCHK(h, hipGetLastError());
@@ -514,7 +511,7 @@ int init_device(pf_lbm *h, const pf_lbm_body *bodies_in, const double *rho0, con
     HIPCHK(h, hipMemsetAsync(fB, 0, (size_t)Lat::Q * h->Np * sizeof(S), s));
     // neighbour bits of the cell words
     if (h->nb > 0)
-        k_post<S, Lat><<<dim3(h->box_grid), b, 0, s>>>(p, 0, st, mask, nbw, fA, psi_init);
+        k_post<Lat><<<dim3(h->box_grid), b, 0, s>>>(p.nx, p.ny, p.nz, st, mask, nbw);
     HIPCHK(h, hipGetLastError());
     HIPCHK(h, hipStreamSynchronize(s));
     return PF_LBM_OK;
