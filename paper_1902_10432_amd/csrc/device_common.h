@@ -85,8 +85,16 @@ struct BodyDev {
 
 // Per-step state shared by the kernels.  Boxes are in unwrapped lattice coordinates
 // [lo, hi] per axis (hi - lo + 1 <= n); box[p] is read by step parity p, written for the next.
+// The run of phase-field tiles that meets a box (TileIter): lower corner and extent of the box, first
+// tile (wrapped) and number of tiles per axis, their product, reciprocals of the x and y counts.
+struct TileRun {
+    int32_t lo[3], ext[3], t0[3], cnt[3], total, pad;
+    double inv0, inv1;
+};
+
 struct StepState {
     int32_t box[2][6];            // lo x, lo y, lo z, hi x, hi y, hi z
+    TileRun tiles[2];             // of the same boxes
     uint32_t err;                 // bit 0 non-finite body state, bit 1 advection CFL above 1
     uint32_t n_events;            // nodes that changed side in this step's reclassification
     uint32_t step_no, pad;        // steps started (counted by the step-state publish)
@@ -259,45 +267,58 @@ __device__ __forceinline__ uint32_t pairs_to_bodies(uint32_t pm) {
     return out;
 }
 
-// the tiles that meet a box [lo, hi] (unwrapped coordinates, at most one period per axis):
-// per axis a run of cnt tiles starting at t0 (wrapped); tile k of the run and the nodes of a tile
+// The tiles that meet a box [lo, hi] (unwrapped coordinates, at most one period per axis, extent 0
+// where empty) of a grid of n nodes and tn tiles: per axis a run of cnt tiles from t0 (wrapped).
+__device__ __forceinline__ void tile_run(const int32_t *b, const int *n, const int *tn, TileRun &r) {
+    const int te[3] = {TLX, TLY, TLZ};
+    r.total = 1;
+    for (int d = 0; d < 3; ++d) {
+        r.lo[d] = b[d];
+        r.ext[d] = b[3 + d] - b[d] + 1;
+        int t0 = 0, c = 0;
+        if (r.ext[d] > 0) {
+            int a = r.lo[d] % n[d];
+            a += a < 0 ? n[d] : 0;
+            const int e = a + r.ext[d] - 1;  // last cell, unwrapped from a
+            const int ta = a / te[d];
+            c = e < n[d] ? e / te[d] - ta + 1 : (tn[d] - ta) + (e - n[d]) / te[d] + 1;
+            if (r.ext[d] >= n[d] || c >= tn[d])
+                c = tn[d];
+            else
+                t0 = ta;
+        }
+        r.t0[d] = t0;
+        r.cnt[d] = c;
+        r.total *= c;
+    }
+    r.pad = 0;
+    r.inv0 = 1.0 / max(r.cnt[0], 1);
+    r.inv1 = 1.0 / max(r.cnt[1], 1);
+}
+
+// iteration over a tile run (published with the step's box, so that no kernel of the step divides for
+// it): tile k of the run and the nodes of a tile
 template <typename T>
 struct TileIter {
     int lo[3], ext[3], n[3], t0[3], cnt[3], tn[3], total;
-    __device__ __forceinline__ TileIter(const int32_t *b, const Prm<T> &p) {
+    double inv0, inv1;
+    __device__ __forceinline__ TileIter(const TileRun &r, const Prm<T> &p) : total(r.total), inv0(r.inv0), inv1(r.inv1) {
         n[0] = p.nx;
         n[1] = p.ny;
         n[2] = p.nz;
-        const int te[3] = {TLX, TLY, TLZ};
-        total = 1;
         for (int d = 0; d < 3; ++d) {
             tn[d] = p.tn[d];
-            lo[d] = b[d];
-            ext[d] = b[3 + d] - b[d] + 1;
-            if (ext[d] <= 0) {
-                total = 0;
-                t0[d] = cnt[d] = 0;
-                continue;
-            }
-            int a = lo[d] % n[d];
-            a += a < 0 ? n[d] : 0;
-            const int e = a + ext[d] - 1;  // last cell, unwrapped from a
-            const int ta = a / te[d];
-            int c = e < n[d] ? e / te[d] - ta + 1 : (tn[d] - ta) + (e - n[d]) / te[d] + 1;
-            if (ext[d] >= n[d] || c >= tn[d]) {
-                t0[d] = 0;
-                c = tn[d];
-            } else {
-                t0[d] = ta;
-            }
-            cnt[d] = c;
-            total *= c;
+            lo[d] = r.lo[d];
+            ext[d] = r.ext[d];
+            t0[d] = r.t0[d];
+            cnt[d] = r.cnt[d];
         }
     }
     // wrapped tile coordinates of run entry k and the tile's linear index
     __device__ __forceinline__ int tile(int k, int *tc) const {
-        const int kx = k % cnt[0], r = k / cnt[0], ky = r % cnt[1], kz = r / cnt[1];
-        const int kk[3] = {kx, ky, kz};
+        // the quotients are exact: k + 1/2 lies at least 1 / (2 cnt) from a multiple of cnt
+        const int q = (int)(((double)k + 0.5) * inv0), kz = (int)(((double)q + 0.5) * inv1);
+        const int kk[3] = {k - q * cnt[0], q - kz * cnt[1], kz};
         for (int d = 0; d < 3; ++d) {
             int t = t0[d] + kk[d];
             tc[d] = t >= tn[d] ? t - tn[d] : t;
@@ -315,6 +336,28 @@ struct TileIter {
             ok = ok && c[d] < n[d];
             // (c - lo) mod n: the box's lo lies within one period below or above the grid
             int m = c[d] - lo[d];
+            m += m < 0 ? n[d] : 0;
+            m += m < 0 ? n[d] : 0;
+            m -= m >= n[d] ? n[d] : 0;
+            u[d] = lo[d] + m;
+            ok = ok && m < ext[d];
+        }
+        return ok;
+    }
+    // node at offset l (within one tile edge outside) of tile tc, periodic: wrapped (c) and unwrapped
+    // (u) coordinates; false when it lies outside the box.  Past the end of a partial tile these are
+    // the periodic images that the tile's last nodes have as neighbours.
+    __device__ __forceinline__ bool local(const int *tc, const int *l, int *c, int *u) const {
+        const int te[3] = {TLX, TLY, TLZ};
+        bool ok = true;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            int v = tc[d] * te[d] + l[d];
+            v += v < 0 ? n[d] : 0;
+            if (v < 0 || v >= 2 * n[d]) v = wrapi(v, n[d]);  // axes shorter than the reach
+            v -= v >= n[d] ? n[d] : 0;
+            c[d] = v;
+            int m = v - lo[d];
             m += m < 0 ? n[d] : 0;
             m += m < 0 ? n[d] : 0;
             m -= m >= n[d] ? n[d] : 0;
@@ -394,15 +437,15 @@ __device__ __forceinline__ int wrap2(int i, int n) {
 // results of the previous step in a fixed order and publish
 //  * this step's box (wave 0): phase-field support + 3-cell margin, the whole axis once it would
 //    wrap onto itself, lower corner brought into [0, n) (so unwrapped coordinates stay below 2 n),
-//    and count the step;
+//    its run of tiles, and count the step;
 //  * per body (waves 1.., round robin; wave 0 alone in a one-wave block): the solid radius
 //    (bounds the repulsion search) and the volume
 //    driving term h_a = (4 eta / pi^2) (V_ref - sum phi_a) / #{phi_floor < phi_a < 1} (Sec. 3.3; 0
 //    without interface nodes), into the body table;
 // and clear the event count for this step's reclassification.  Each lane sums its parts with four
 // independent accumulators, then a fixed xor-shuffle tree combines the lanes.
-__device__ __forceinline__ void publish_step_state(int wave, int nwaves, int parity, int nx, int ny, int nz, int nb,
-                                                   double eta, StepState *st, BodyDev *bodies,
+__device__ __forceinline__ void publish_step_state(int wave, int nwaves, int parity, int nx, int ny, int nz,
+                                                   const int *tn, int nb, double eta, StepState *st, BodyDev *bodies,
                                                    const ClassifyPart *cpart, int nblk) {
     const int lane = (int)(threadIdx.x & 63);
     if (wave == 0) {
@@ -419,6 +462,7 @@ __device__ __forceinline__ void publish_step_state(int wave, int nwaves, int par
         if (lane == 0) {
             const int n[3] = {nx, ny, nz};
             const bool empty = lo[0] > hi[0] || lo[1] > hi[1] || lo[2] > hi[2];
+            int32_t b[6];
             for (int d = 0; d < 3; ++d) {
                 int l = lo[d] - 3, h = hi[d] + 3;
                 if (h - l + 1 >= n[d]) {
@@ -429,9 +473,13 @@ __device__ __forceinline__ void publish_step_state(int wave, int nwaves, int par
                     l += s;
                     h += s;
                 }
-                st->box[parity][d] = empty ? 0 : l;
-                st->box[parity][3 + d] = empty ? -1 : h;
+                b[d] = empty ? 0 : l;
+                b[3 + d] = empty ? -1 : h;
             }
+            TileRun r;
+            tile_run(b, n, tn, r);
+            for (int d = 0; d < 6; ++d) st->box[parity][d] = b[d];
+            st->tiles[parity] = r;
             st->n_events = 0u;
             st->step_no += 1u;
         }

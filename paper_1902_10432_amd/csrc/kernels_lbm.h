@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY>(
     const int tid = (int)threadIdx.x, tx = tid & 63, wv = tid >> 6;
     const int extra = cpart ? 1 : 0;
     if (extra && blockIdx.x == 0) {
-        publish_step_state(wv, W, parity, p.nx, p.ny, p.nz, p.nb, p.eta, st, bodies, cpart, cblk);
+        publish_step_state(wv, W, parity, p.nx, p.ny, p.nz, p.tn, p.nb, p.eta, st, bodies, cpart, cblk);
         return;
     }
     // FP16 form: the bodies' motion for the moving-wall term into LDS (ordered before its first

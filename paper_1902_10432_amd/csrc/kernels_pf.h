@@ -20,12 +20,36 @@ __device__ __forceinline__ T mc_slope(T dl, T dr) {
     return dl > T(0) ? m : -m;
 }
 
-// flux through face i+1/2 from the four values i-1, i, i+1, i+2 for velocity u (|u| <= 1):
-// u [phi_up +- (1 - |u|) s_up / 2] with the upwind cell's MC slope (second-order, TVD)
-template <typename T>
-__device__ __forceinline__ T mc_flux(T u, T am1, T a0, T a1, T a2) {
-    if (u >= T(0)) return u * (a0 + T(0.5) * (T(1) - u) * mc_slope(a0 - am1, a1 - a0));
-    return u * (a1 - T(0.5) * (T(1) + u) * mc_slope(a1 - a0, a2 - a1));
+// One conservative sweep at a cell from the five values i-2..i+2 along the axis for velocity u
+// (|u| <= 1): v0 - (F_{i+1/2} - F_{i-1/2}), the flux through a face u [phi_up +- (1 - |u|) s_up / 2] with
+// the upwind cell's MC slope (second-order, TVD).  For u < 0 the stencil is mirrored, which negates
+// both fluxes exactly, so that two slopes are formed whatever the sign and lanes do not diverge.
+__device__ __forceinline__ double sweep5(double u, double vm2, double vm1, double v0, double v1, double v2) {
+    const bool pos = u >= 0.0;
+    const double w = fabs(u), b2 = pos ? vm2 : v2, b1 = pos ? vm1 : v1, a1 = pos ? v1 : vm1;
+    const double k = 0.5 * (1.0 - w);
+    const double out = w * (v0 + k * mc_slope(v0 - b1, a1 - v0)), in = w * (b1 + k * mc_slope(b1 - b2, v0 - b1));
+    return v0 - (out - in);
+}
+
+// X, V, W of every body into LDS (table [body][9]); whole block
+__device__ __forceinline__ void stage_motion(const BodyDev *next, int nbod, double (*lb)[9]) {
+    for (int k = threadIdx.x; k < nbod * 9; k += blockDim.x) {
+        const BodyDev &B = next[k / 9];
+        const int c = k % 9;
+        lb[k / 9][c] = c < 3 ? B.X[c] : (c < 6 ? B.V[c - 3] : B.W[c - 6]);
+    }
+}
+
+// component AX of body a's rigid velocity at a node with wrapped coordinates c (it does not vary along
+// AX)
+template <int AX, typename T>
+__device__ __forceinline__ double sweep_velocity(const Prm<T> &p, const double *b, const int *c) {
+    constexpr int A1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
+    const int n[3] = {p.nx, p.ny, p.nz};
+    const double r1 = mimg_r((double)c[A1] - b[A1], n[A1], p.inv_n[A1]);
+    const double r2 = mimg_r((double)c[A2] - b[A2], n[A2], p.inv_n[A2]);
+    return b[3 + AX] + (b[6 + A1] * r2 - b[6 + A2] * r1);
 }
 
 // Sum K values of per-block partials part[k * nblk + j], nblk <= 256, into out[k] with a block of
@@ -51,62 +75,62 @@ __device__ __forceinline__ void block_totals(const double *part, int nblk, int K
     __syncthreads();
 }
 
-// One directional sweep (axis AX) of d phi_a/dt = -u_B . grad phi_a in conservative form for
-// every body a: phi_i -= F_{i+1/2} - F_{i-1/2}.  The rigid velocity component along the sweep
-// does not vary along the sweep line, so the update is exactly conservative.  The bodies' motion
-// is that of the rigid-body update of this step (the next table).  The sweep visits the tiles of
-// the box, one per block, and on each only the bodies active there (tact, pair form); elsewhere
-// its update is the identity.
-template <typename T, int AX, int NBMAX>
-__global__ __launch_bounds__(256) void k_advect(Prm<T> p, int parity, StepState *st, const BodyDev *__restrict__ next,
-                                                const double *__restrict__ src, double *__restrict__ dst,
-                                                const uint32_t *__restrict__ tact) {
-    __shared__ double lb[PF_LBM_MAX_BODIES][9];  // X, V, W of each body for this sweep
-    const int tid = threadIdx.x;
-    const int nbod = p.nb;
-    // the box words are read first so that their latency overlaps the body-table reads
-    int32_t box[6];
-    for (int d = 0; d < 6; ++d) box[d] = st->box[parity][d];
-    if (tid < nbod)
-        for (int d = 0; d < 3; ++d) {
-            lb[tid][d] = next[tid].X[d];
-            lb[tid][3 + d] = next[tid].V[d];
-            lb[tid][6 + d] = next[tid].W[d];
-        }
+// The x and y sweeps of d phi_a/dt = -u_B . grad phi_a in conservative form for every body a: phi_i -=
+// F_{i+1/2} - F_{i-1/2}.  The rigid velocity component along a sweep does not vary along the sweep line,
+// so the update is exactly conservative.  The bodies' motion is that of the rigid-body update of this
+// step (the next table).  A block takes a tile of the box and the bodies active there (tact, pair form;
+// elsewhere the sweeps are the identity and both buffers hold the constant): the x sweep of the tile
+// and of the two rows on either side goes to LDS, from which the y sweep reads, so that the two cost
+// one launch and one trip through memory (the rows beside it, half a tile more, are swept twice).  The z
+// sweep is part of the phase update.
+//
+// Bound by the latency of one chain of loads per tile and by FP64 issue.  Three sweeps of a launch
+// each, with the stencils of four bodies loaded whether active or not, and the phase update without
+// the z sweep took 26.2 us at 61 x 45 x 50 (two spheres), 38.7 at 128^3 and 118 at 256^3 (four spheres);
+// this kernel and the phase update take 20.2, 33.6 and 86.5, and two launches less.
+// One entry of the x sweep per thread: 8 x 12 x 4.
+constexpr int XY_THREADS = TLX * (TLY + 4) * TLZ;
+
+template <typename T, int NBMAX>
+__global__ __launch_bounds__(XY_THREADS) void k_advect_xy(Prm<T> p, int parity, StepState *st,
+                                                          const BodyDev *__restrict__ next, const double *__restrict__ src,
+                                                          double *__restrict__ dst, const uint32_t *__restrict__ tact) {
+    constexpr int G = NBMAX < 2 ? NBMAX : 2;  // bodies per round
+    __shared__ double lb[PF_LBM_MAX_BODIES][9];
+    __shared__ double xs[G][TLZ][TLY + 4][TLX];
+    const int tid = threadIdx.x, nbod = p.nb;
+    const TileIter<T> ti(st->tiles[parity], p);
+    stage_motion(next, nbod, lb);
     __syncthreads();
-    const TileIter<T> ti(box, p);
-    const int n[3] = {p.nx, p.ny, p.nz};
+    const int nx = p.nx, ny = p.ny;
     const long long Np = p.Np;
-    const int step = AX == 0 ? 1 : (AX == 1 ? p.nx : p.nx * p.ny);
-    const int L = n[AX];
-    constexpr int A1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
     const uint32_t pm = pair_mask(nbod);
     uint32_t cfl = 0;
     const int bid = xcd_block(blockIdx.x, gridDim.x);
+    const int lx = tid % TLX, ly = (tid / TLX) % (TLY + 4), lz = tid / (TLX * (TLY + 4));
     for (int tk = bid; tk < ti.total; tk += gridDim.x) {
         int tc[3];
         const int tl = ti.tile(tk, tc);
         uint32_t am = pairs_to_bodies(tact[tl] & pm);  // bodies active on the tile (uniform)
         if (!am) continue;
-        int u[3], c[3];
-        const bool ok = ti.node(tc, tid, c, u);
-        // threads off the grid or the box address node 0 and discard what they load
-        const int idx = ok ? c[0] + p.nx * (c[1] + p.ny * c[2]) : 0;
-        const int i = ok ? c[AX] : 0;
-        // flat indices of the five cells i-2..i+2 along the axis (periodic); cells outside the
-        // box hold no phase (the support stays 3 cells inside it through the step) and are not
-        // read, so the intermediate buffers need no clearing outside the box
-        int off[5];
+        // this thread's entry of the x sweep; threads whose entry lies outside the box address node 0
+        // and discard what they load
+        const int l[3] = {lx, ly - 2, lz};
+        int ec[3], eu[3], off[5];
+        const bool ok = ti.local(tc, l, ec, eu);
         bool in[5];
+        {
+            const int row = ok ? nx * (ec[1] + ny * ec[2]) : 0, x = ok ? ec[0] : 0;
 #pragma unroll
-        for (int s = -2; s <= 2; ++s) {
-            off[s + 2] = idx + (wrap2(i + s, L) - i) * step;
-            in[s + 2] = ok && ti.inside(AX, u[AX] + s);
+            for (int s = -2; s <= 2; ++s) {
+                off[s + 2] = row + wrap2(x + s, nx);
+                in[s + 2] = ok && ti.inside(0, eu[0] + s);
+            }
         }
-        // the stencils of up to four active phases first, loaded unconditionally (the wrapped
-        // indices lie in the grid; values outside the box are masked), so that one memory latency
-        // covers the group
-        constexpr int G = NBMAX < 4 ? NBMAX : 4;
+        // the threads of the eight inner rows also take the y sweep of their node (a node of a partial
+        // tile past the grid's edge belongs to another tile)
+        const bool mine = ok && ly >= 2 && ly < TLY + 2 && tc[0] * TLX + lx < nx && tc[1] * TLY + ly - 2 < ny &&
+                          tc[2] * TLZ + lz < p.nz;
         while (am) {
             int ag[G];
 #pragma unroll
@@ -116,29 +140,39 @@ __global__ __launch_bounds__(256) void k_advect(Prm<T> p, int parity, StepState 
             }
             double sv[G][5];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const double *s0 = src + (long long)(ag[g] >= 0 ? ag[g] : ag[0]) * Np;
+            for (int g = 0; g < G; ++g)
+                if (g == 0 || ag[g] >= 0) {  // uniform
+                    const double *s0 = src + (long long)ag[g] * Np;
 #pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    const double t = s0[off[q]];
-                    sv[g][q] = in[q] ? t : 0.0;
+                    for (int q = 0; q < 5; ++q) sv[g][q] = s0[off[q]];
                 }
-            }
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int a = ag[g];
-                if (a < 0) break;
-                if (!ok) continue;
-                // velocity component along AX at this sweep line
-                const double r1 = mimg_r((double)c[A1] - lb[a][A1], n[A1], p.inv_n[A1]);
-                const double r2 = mimg_r((double)c[A2] - lb[a][A2], n[A2], p.inv_n[A2]);
-                const double uu = lb[a][3 + AX] + (lb[a][6 + A1] * r2 - lb[a][6 + A2] * r1);
-                const double vm2 = sv[g][0], vm1 = sv[g][1], v0 = sv[g][2], v1 = sv[g][3], v2 = sv[g][4];
-                const double Fp = mc_flux(uu, vm1, v0, v1, v2);
-                const double Fm = mc_flux(uu, vm2, vm1, v0, v1);
-                dst[(long long)a * Np + idx] = v0 - (Fp - Fm);
-                if (fabs(uu) > 1.0 && (vm2 != 0.0 || vm1 != 0.0 || v0 != 0.0 || v1 != 0.0 || v2 != 0.0)) cfl = 1;
-            }
+            for (int g = 0; g < G; ++g)
+                if (g == 0 || ag[g] >= 0) {
+                    double v[5], r = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) v[q] = in[q] ? sv[g][q] : 0.0;
+                    if (ok) {
+                        const double uu = sweep_velocity<0>(p, lb[ag[g]], ec);
+                        r = sweep5(uu, v[0], v[1], v[2], v[3], v[4]);
+                        if (mine && fabs(uu) > 1.0 &&
+                            (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0 || v[3] != 0.0 || v[4] != 0.0))
+                            cfl = 1;
+                    }
+                    xs[g][lz][ly][lx] = r;
+                }
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                if ((g == 0 || ag[g] >= 0) && mine) {
+                    double v[5];
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) v[q] = ti.inside(1, eu[1] + q - 2) ? xs[g][lz][ly + q - 2][lx] : 0.0;
+                    const double uu = sweep_velocity<1>(p, lb[ag[g]], ec);
+                    dst[(long long)ag[g] * Np + off[2]] = sweep5(uu, v[0], v[1], v[2], v[3], v[4]);
+                    if (fabs(uu) > 1.0 && (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0 || v[3] != 0.0 || v[4] != 0.0)) cfl = 1;
+                }
+            __syncthreads();
         }
     }
     if (cfl) atomicOr(&st->err, 2u);  // rare: only when the input breaks the CFL bound
@@ -236,9 +270,9 @@ struct ClassAcc {
     uint32_t f2s, s2f;
     float rad[NBMAX];
     double vol[NBMAX];
-    uint32_t icnt[NBMAX];
+    int *icnt;  // interface nodes per body, in LDS (whole numbers: the order does not matter)
 
-    __device__ __forceinline__ ClassAcc() {
+    __device__ __forceinline__ explicit ClassAcc(int *icnt_) : icnt(icnt_) {
         for (int d = 0; d < 3; ++d) {
             lo[d] = INT32_MAX;
             hi[d] = INT32_MIN;
@@ -248,31 +282,34 @@ struct ClassAcc {
         for (int a = 0; a < NBMAX; ++a) {
             rad[a] = 0.0f;
             vol[a] = 0.0;
-            icnt[a] = 0u;
         }
     }
 
     // Solid iff the fluid fraction 1 - sum phi is below the threshold, owner = argmax phi (lowest
     // index on ties; Sec. 3.2.2).  Updates the cell word (marks a change of side) and returns the
     // event-list entry + 1 of a node that changed side (bit 31: it became solid), else 0.
-    // old: the node's cell word, read by the caller ahead of the phase loads
-    template <typename PT>
+    // old: the node's cell word, read by the caller ahead of the phase loads; out: phases of the K
+    // bodies ids (ascending, uniform), every other body being zero at the node
+    template <int K, typename PT>
     __device__ __forceinline__ uint32_t node(const Prm<PT> &p, const BodyDev *__restrict__ bodies,
                                              cell_t *__restrict__ mask, int idx, const int *u, const int *c,
-                                             const double *out, cell_t old) {
+                                             const int (&ids)[K], const double *out, cell_t old) {
         const int nbod = p.nb;
         double sum = 0.0, best = -1.0;
         int arg = 0;
 #pragma unroll
-        for (int a = 0; a < NBMAX; ++a) {
-            if (a >= nbod) break;
-            sum += out[a];
-            if (out[a] > best) {
-                best = out[a];
-                arg = a;
+        for (int k = 0; k < K; ++k) {
+            if (ids[k] >= nbod) break;
+            sum += out[k];
+            if (out[k] > best) {
+                best = out[k];
+                arg = ids[k];
             }
-            vol[a] += out[a];
-            icnt[a] += (out[a] > p.phi_floor && out[a] < 1.0) ? 1u : 0u;
+            const uint64_t itf = __ballot(out[k] > p.phi_floor && out[k] < 1.0);
+            if (itf && (int)(threadIdx.x & 63) == (int)__builtin_ctzll(itf)) atomicAdd(&icnt[ids[k]], __popcll(itf));
+#pragma unroll
+            for (int a = 0; a < NBMAX; ++a)
+                if (a == ids[k]) vol[a] += out[k];
         }
         const bool solid = nbod > 0 && (1.0 - sum) < p.threshold;
         uint32_t event = 0;
@@ -295,8 +332,12 @@ struct ClassAcc {
                          rz = mimg_r(c[2] - B.X[2], p.nz, p.inv_n[2]);
             const float r = (float)sqrt(rx * rx + ry * ry + rz * rz) + 1e-3f;
 #pragma unroll
-            for (int a = 0; a < NBMAX; ++a)
-                if (a == arg) rad[a] = fmaxf(rad[a], r);
+            for (int a = 0; a < NBMAX; ++a) {
+                // a select: the compiler turns a branch into an indexed store, and the array into scratch memory
+                float ra = a == arg ? r : 0.0f;
+                asm volatile("" : "+v"(ra));
+                rad[a] = fmaxf(rad[a], ra);
+            }
         }
         if (sum > 0.0)
             for (int d = 0; d < 3; ++d) {
@@ -306,38 +347,38 @@ struct ClassAcc {
         return event;
     }
 
-    // whole block (256 threads, uniform call): cpart[blockIdx.x] and the conversion counters
-    __device__ void finish(int nbod, StepState *st, ClassifyPart *cpart) {
+    // four waves (uniform call; other waves of the block take part in the barrier with on = false):
+    // cpart[blockIdx.x] and the conversion counters
+    __device__ __forceinline__ void finish(int nbod, StepState *st, ClassifyPart *cpart, bool on4) {
         __shared__ int32_t sb[4][6];
         __shared__ uint32_t sc[4][2];
         __shared__ float sr[4][NBMAX];
         __shared__ double sv[4][NBMAX];
-        __shared__ uint32_t si[4][NBMAX];
         const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-        for (int d = 0; d < 3; ++d) {
-            const int l = wave_min(lo[d]), h = wave_max(hi[d]);
-            if (lane == 0) {
-                sb[wave][d] = l;
-                sb[wave][3 + d] = h;
+        if (on4) {
+            for (int d = 0; d < 3; ++d) {
+                const int l = wave_min(lo[d]), h = wave_max(hi[d]);
+                if (lane == 0) {
+                    sb[wave][d] = l;
+                    sb[wave][3 + d] = h;
+                }
             }
-        }
-        const uint32_t a2 = (uint32_t)wave_sum((int)f2s), b2 = (uint32_t)wave_sum((int)s2f);
-        if (lane == 0) {
-            sc[wave][0] = a2;
-            sc[wave][1] = b2;
-        }
-#pragma unroll
-        for (int a = 0; a < NBMAX; ++a) {
-            if (a >= nbod) break;
-            float r = rad[a];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) r = fmaxf(r, __shfl_xor(r, off, 64));
-            const double v = wave_sum(vol[a]);
-            const int ic = wave_sum((int)icnt[a]);
+            const uint32_t a2 = (uint32_t)wave_sum((int)f2s), b2 = (uint32_t)wave_sum((int)s2f);
             if (lane == 0) {
-                sr[wave][a] = r;
-                sv[wave][a] = v;
-                si[wave][a] = (uint32_t)ic;
+                sc[wave][0] = a2;
+                sc[wave][1] = b2;
+            }
+#pragma unroll
+            for (int a = 0; a < NBMAX; ++a) {
+                if (a >= nbod) break;
+                float r = rad[a];
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) r = fmaxf(r, __shfl_xor(r, off, 64));
+                const double v = wave_sum(vol[a]);
+                if (lane == 0) {
+                    sr[wave][a] = r;
+                    sv[wave][a] = v;
+                }
             }
         }
         __syncthreads();
@@ -353,7 +394,7 @@ struct ClassAcc {
                 const bool on = b < nbod;
                 cp.srad[b] = on ? fmaxf(fmaxf(sr[0][b], sr[1][b]), fmaxf(sr[2][b], sr[3][b])) : 0.0f;
                 cp.vol[b] = on ? ((sv[0][b] + sv[1][b]) + sv[2][b]) + sv[3][b] : 0.0;
-                cp.icnt[b] = on ? si[0][b] + si[1][b] + si[2][b] + si[3][b] : 0u;
+                cp.icnt[b] = on ? (uint32_t)icnt[b] : 0u;
             }
             cpart[blockIdx.x] = cp;
             if (cp.f2s + cp.s2f) {  // rare: nodes of this block changed side
@@ -379,15 +420,91 @@ __device__ __forceinline__ void append_events(StepState *st, uint32_t *evlist, u
     }
 }
 
-// Phase update after the advection sweeps, one tile of the box per block and one node per thread,
-// on the tiles where some body is active: kinetics (kinetics_node; without kinetics the phases
-// pass unchanged), reclassification with the event list, per-block partials, and the tile's new
-// state word.  Bodies inactive on the tile hold their tile constant at every node the stencil
-// reaches, so their values are taken from the state word instead of memory.  On a tile where
-// no body is active nothing changes; the bodies that fill it (phi = 1) add its node count to
-// their volume sums.  Face neighbours outside the box hold no phase and are not read.
+// Kinetics, write-back and classification of one node on the K bodies ids of its tile (ascending,
+// uniform; ids >= nb end the list), every other body being zero at the node and around it.
+// zs[k]: body ids[k] after the sweeps, on the tile and its face neighbours.  Returns the event entry.
+template <int K, int NBMAX, typename PT>
+__device__ __forceinline__ uint32_t phase_node(const Prm<PT> &p, const int (&ids)[K], const double (*zs)[TLZ + 2][TLY + 2][TLX + 2],
+                                               const int *l, const double *sg, const double *hh, bool kin, double mu,
+                                               double vterm, const BodyDev *__restrict__ bodies, cell_t *__restrict__ mask,
+                                               double *__restrict__ dst, int idx, const int *u, const int *c, cell_t old,
+                                               ClassAcc<NBMAX> &acc, uint32_t &bits) {
+    constexpr int NP = NBMAX + 1, NK = K + 1;
+    double v[K], out[K];
+    int nk = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool on = ids[k] < p.nb;
+        nk += on ? 1 : 0;
+        v[k] = on ? zs[k][l[2] + 1][l[1] + 1][l[0] + 1] : 0.0;
+        out[k] = v[k];
+    }
+    if (kin) {
+        if constexpr (K == NBMAX) {
+            kinetics_node<K>(
+                v,
+                [&](int e, int k) {
+                    const int dx = e == 0 ? 1 : (e == 1 ? -1 : 0), dy = e == 2 ? 1 : (e == 3 ? -1 : 0),
+                              dz = e == 4 ? 1 : (e == 5 ? -1 : 0);
+                    return ids[k] < p.nb ? zs[k][l[2] + 1 + dz][l[1] + 1 + dy][l[0] + 1 + dx] : 0.0;
+                },
+                nk, sg, hh, mu, vterm, p.mobility, p.phi_floor, out);
+        } else {
+            // interface energies and driving terms of the subset
+            double sk[NK * NK], hk[NK];
+            hk[0] = 0.0;
+#pragma unroll
+            for (int a = 0; a < NK; ++a)
+#pragma unroll
+                for (int b = 0; b < NK; ++b)
+                    sk[a * NK + b] = sg[(a ? min(ids[a - 1], NBMAX - 1) + 1 : 0) * NP + (b ? min(ids[b - 1], NBMAX - 1) + 1 : 0)];
+#pragma unroll
+            for (int a = 1; a < NK; ++a) hk[a] = hh[min(ids[a - 1], NBMAX - 1) + 1];
+            kinetics_node<K>(
+                v,
+                [&](int e, int k) {
+                    const int dx = e == 0 ? 1 : (e == 1 ? -1 : 0), dy = e == 2 ? 1 : (e == 3 ? -1 : 0),
+                              dz = e == 4 ? 1 : (e == 5 ? -1 : 0);
+                    return ids[k] < p.nb ? zs[k][l[2] + 1 + dz][l[1] + 1 + dy][l[0] + 1 + dx] : 0.0;
+                },
+                nk, sk, hk, mu, vterm, p.mobility, p.phi_floor, out);
+        }
+    }
+    // the tile's state bits: bodies outside the list are zero (pair bits 10)
+    bits = pair_mask(p.nb) << 1;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (ids[k] < p.nb) {
+            dst[(long long)ids[k] * p.Np + idx] = out[k];
+            bits |= (out[k] != 0.0 ? 1u : 0u) << (2 * ids[k]);
+            if (out[k] == 1.0) bits &= ~(2u << (2 * ids[k]));
+        }
+    return acc.template node<K>(p, bodies, mask, idx, u, c, ids, out, old);
+}
+
+// Phase update after the x and y sweeps, one tile of the box per block and one node per thread, on the
+// tiles where some body is active: the z sweep of the active bodies on the tile and its face
+// neighbours into LDS (512 values, so a tile's worth is swept twice), kinetics
+// from there (kinetics_node; without kinetics the phases pass unchanged), reclassification with the
+// event list, per-block partials, and the tile's new state word.  Where few bodies are active (one of
+// two, up to two of four, up to four of more) and the others are zero (nearly every tile) only those are treated, which gives the same sums, as
+// absent phases enter none.  A body inactive on the tile holds its tile constant at every node the
+// stencil reaches; a constant one is taken from the state word, on the general path.  On a tile where no
+// body is active nothing changes; the bodies that fill it (phi = 1) add its node count to their volume
+// sums.  Nodes outside the box hold no phase and are not read.
+// Threads of a block: with up to two bodies 512, one z-sweep value each (a shorter path where latency
+// counts), else 256 with two each.  The registers are kept to what lets two (three) blocks share a CU.
+template <int NBMAX>
+constexpr int phase_threads() {
+    return NBMAX <= 2 ? 512 : 256;
+}
+template <int NBMAX>
+constexpr int phase_min_waves() {
+    return NBMAX <= 2 ? 4 : (NBMAX <= 4 ? 3 : 1);
+}
+
 template <typename PT, int NBMAX>
-__global__ __launch_bounds__(256) void k_phase_update(Prm<PT> p, int parity, StepState *st,
+__global__ __launch_bounds__((phase_threads<NBMAX>()), (phase_min_waves<NBMAX>())) void k_phase_update(Prm<PT> p, int parity, StepState *st,
                                                       const BodyDev *__restrict__ bodies,
                                                       const double *__restrict__ sigma, const double *__restrict__ src,
                                                       double *__restrict__ dst, cell_t *__restrict__ mask,
@@ -397,26 +514,30 @@ __global__ __launch_bounds__(256) void k_phase_update(Prm<PT> p, int parity, Ste
     constexpr int NP = NBMAX + 1;
     __shared__ double sg[NP * NP];
     __shared__ double hh[NP];
+    __shared__ int icnt[PF_LBM_MAX_BODIES];
+    __shared__ double lb[PF_LBM_MAX_BODIES][9];
+    __shared__ double zs[NBMAX][TLZ + 2][TLY + 2][TLX + 2];
+    constexpr int TPB = phase_threads<NBMAX>(), NH = 512 / TPB;
     const int tid = threadIdx.x;
     const int nbod = p.nb, np1 = nbod + 1;
-    // the box words are read first so that their latency overlaps the table reads
-    int32_t box[6];
-    for (int d = 0; d < 6; ++d) box[d] = st->box[parity][d];
-    for (int k = tid; k < NP * NP; k += 256) {
+    const TileIter<PT> ti(st->tiles[parity], p);
+    stage_motion(bodies, nbod, lb);
+    for (int k = tid; k < NP * NP; k += TPB) {
         const int r = k / NP, c = k % NP;
         sg[k] = (r < np1 && c < np1) ? sigma[r * np1 + c] : 0.0;
     }
+    if (tid < PF_LBM_MAX_BODIES) icnt[tid] = 0;
     if (tid < NP) hh[tid] = (tid == 0 || tid > nbod) ? 0.0 : bodies[tid - 1].h;
     __syncthreads();
-    const TileIter<PT> ti(box, p);
-    const int nx = p.nx, ny = p.ny, nz = p.nz;
+    const int nx = p.nx, ny = p.ny, nz = p.nz, pl = nx * ny;
     const long long Np = p.Np;
     const bool kin = (p.flags & PF_LBM_KINETICS) != 0;
     const double PI = 3.14159265358979323846;
-    const double mu = PI * PI / (p.eta * p.eta), vterm = PI * PI / (4.0 * p.eta), M = p.mobility;
+    const double mu = PI * PI / (p.eta * p.eta), vterm = PI * PI / (4.0 * p.eta);
     const uint32_t pm = pair_mask(nbod);
     const int wave = tid >> 6, lane = tid & 63;
-    ClassAcc<NBMAX> acc;
+    ClassAcc<NBMAX> acc(icnt);
+    uint32_t cfl = 0;
     const int bid = xcd_block(blockIdx.x, gridDim.x);
     for (int tk = bid; tk < ti.total; tk += gridDim.x) {
         int tc[3];
@@ -424,63 +545,131 @@ __global__ __launch_bounds__(256) void k_phase_update(Prm<PT> p, int parity, Ste
         const uint32_t act = tact[tl] & pm;  // uniform
         const uint4 sw = tstate[tl];
         const uint32_t s0 = (sw.x | sw.y) | (sw.z | sw.w);
+        // bodies inactive here that fill the tile (state 01)
+        const uint32_t full = s0 & ~(s0 >> 1) & pm & ~act;
         if (!act) {
             if (tid == 0) {
                 const int cnt = min(TLX, nx - tc[0] * TLX) * min(TLY, ny - tc[1] * TLY) * min(TLZ, nz - tc[2] * TLZ);
 #pragma unroll
                 for (int a = 0; a < NBMAX; ++a)
-                    if (a < nbod && ((s0 >> (2 * a)) & 3u) == 1u) acc.vol[a] += (double)cnt;
+                    if (a < nbod && ((full >> (2 * a)) & 1u)) acc.vol[a] += (double)cnt;
             }
             continue;
         }
-        uint32_t event = 0, bits = 0;
+        // threads 0..255: the nodes of the tile
         int u[3], c[3];
-        const bool ok = ti.node(tc, tid, c, u);
-        if (ok) {
-            const int idx = c[0] + nx * (c[1] + ny * c[2]);
-            const cell_t old = mask[idx];  // issued with the phase loads
-            double v[NBMAX], out[NBMAX], cst[NBMAX];
-            bool on[NBMAX];
+        const bool ok = ti.node(tc, tid & 255, c, u) && tid < 256;
+        const int idx = ok ? c[0] + nx * (c[1] + ny * c[2]) : 0;
+        const cell_t old = mask[idx];  // issued with the phase loads
+        // the bodies of the tile: the active ones, or on the general path every body
+        const uint32_t ab = pairs_to_bodies(act);
+        const int na = __popc(ab);
+        constexpr int FEW = NBMAX > 4 ? 4 : (NBMAX > 2 ? 2 : (NBMAX > 1 ? 1 : 0));
+        const bool few = !full && na <= FEW;
+        // ---- z sweep of the tile (first half) and of its six faces (second half)
+        {
+            int el[NH][3], ec[NH][3], off[NH][5];
+            bool eok[NH], in[NH][5];
 #pragma unroll
-            for (int a = 0; a < NBMAX; ++a) {
-                on[a] = a < nbod && ((act >> (2 * a)) & 1u);
-                cst[a] = (a < nbod && ((s0 >> (2 * a)) & 3u) == 1u) ? 1.0 : 0.0;
-                v[a] = on[a] ? src[(long long)a * Np + idx] : cst[a];
-                out[a] = v[a];
-            }
-            if (kin) {
-                const Nbr nb(c[0], c[1], c[2], nx, ny, nz);
-                const int offs[6] = {nb.xp, nb.xm, nb.yp, nb.ym, nb.zp, nb.zm};
-                const bool ins[6] = {ti.inside(0, u[0] + 1), ti.inside(0, u[0] - 1), ti.inside(1, u[1] + 1),
-                                     ti.inside(1, u[1] - 1), ti.inside(2, u[2] + 1), ti.inside(2, u[2] - 1)};
-                kinetics_node<NBMAX>(
-                    v,
-                    [&](int e, int a) {
-                        return on[a] ? (ins[e] ? src[(long long)a * Np + idx + offs[e]] : 0.0) : cst[a];
-                    },
-                    nbod, sg, hh, mu, vterm, M, p.phi_floor, out);
-            }
-            // every body is written: a body inactive here keeps its constant, except where the
-            // final rescale of the solids moves it by rounding (its state word then shows it)
-#pragma unroll
-            for (int a = 0; a < NBMAX; ++a)
-                if (a < nbod) {
-                    dst[(long long)a * Np + idx] = out[a];
-                    bits |= (out[a] != 0.0 ? 1u : 0u) << (2 * a);
-                    bits |= (out[a] != 1.0 ? 2u : 0u) << (2 * a);
+            for (int h = 0; h < NH; ++h) {
+                const int e = tid + TPB * h, f = e & 255;
+                if (e < 256) {  // nodes of the tile
+                    el[h][0] = e & 7;
+                    el[h][1] = (e >> 3) & 7;
+                    el[h][2] = e >> 6;
+                } else if (f < 128) {  // x and y faces, 8 x 4 nodes
+                    const int side = (f & 32) ? 8 : -1, r = f & 31;
+                    el[h][0] = f < 64 ? side : r & 7;
+                    el[h][1] = f < 64 ? r & 7 : side;
+                    el[h][2] = r >> 3;
+                } else {  // z faces, 8 x 8 nodes
+                    el[h][0] = f & 7;
+                    el[h][1] = (f >> 3) & 7;
+                    el[h][2] = f < 192 ? -1 : TLZ;
                 }
-            event = acc.node(p, bodies, mask, idx, u, c, out, old);
+                int eu[3];
+                eok[h] = ti.local(tc, el[h], ec[h], eu);
+                const int col = eok[h] ? ec[h][0] + nx * ec[h][1] : 0, z = eok[h] ? ec[h][2] : 0;
+#pragma unroll
+                for (int s = -2; s <= 2; ++s) {
+                    off[h][s + 2] = col + pl * wrap2(z + s, nz);
+                    in[h][s + 2] = eok[h] && ti.inside(2, eu[2] + s);
+                }
+            }
+            int k = 0;
+            for (uint32_t m = few ? ab : (nbod >= 32 ? 0xFFFFFFFFu : (1u << nbod) - 1u); m; m &= m - 1, ++k) {
+                const int a = __ffs(m) - 1;  // uniform
+                if (!((ab >> a) & 1u)) {
+                    const double cst = ((full >> (2 * a)) & 1u) ? 1.0 : 0.0;
+#pragma unroll
+                    for (int h = 0; h < NH; ++h)
+                        zs[k][el[h][2] + 1][el[h][1] + 1][el[h][0] + 1] = cst;
+                    continue;
+                }
+                const double *s0p = src + (long long)a * Np;
+                double sv[NH][5];
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) sv[h][q] = s0p[off[h][q]];
+                const double *b = lb[a];
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    double v[5], r = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) v[q] = in[h][q] ? sv[h][q] : 0.0;
+                    if (eok[h]) {
+                        const double uu = sweep_velocity<2>(p, b, ec[h]);
+                        r = sweep5(uu, v[0], v[1], v[2], v[3], v[4]);
+                        if (h == 0 && ok && fabs(uu) > 1.0 &&
+                            (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0 || v[3] != 0.0 || v[4] != 0.0))
+                            cfl = 1;
+                    }
+                    zs[k][el[h][2] + 1][el[h][1] + 1][el[h][0] + 1] = r;
+                }
+            }
+        }
+        __syncthreads();
+        uint32_t event = 0, bits = 0;
+        if (ok) {
+            const int l[3] = {tid & 7, (tid >> 3) & 7, tid >> 6};
+            if (few) {
+                const int a0 = __ffs(ab) - 1;
+                if (na == 1) {
+                    const int ids[1] = {a0};
+                    event = phase_node<1, NBMAX>(p, ids, zs, l, sg, hh, kin, mu, vterm, bodies, mask, dst, idx, u, c, old, acc, bits);
+                } else if constexpr (NBMAX > 2) {
+                    if (NBMAX <= 4 || na == 2) {
+                        const int ids[2] = {a0, 31 - __clz(ab)};
+                        event = phase_node<2, NBMAX>(p, ids, zs, l, sg, hh, kin, mu, vterm, bodies, mask, dst, idx, u, c, old, acc, bits);
+                    } else if constexpr (NBMAX > 4) {
+                        // three or four (a list of three ends with an absent body)
+                        const uint32_t r1 = ab & (ab - 1), r2 = r1 & (r1 - 1), r3 = r2 & (r2 - 1);
+                        const int ids[4] = {a0, __ffs(r1) - 1, __ffs(r2) - 1, r3 ? __ffs(r3) - 1 : PF_LBM_MAX_BODIES};
+                        event = phase_node<4, NBMAX>(p, ids, zs, l, sg, hh, kin, mu, vterm, bodies, mask, dst, idx, u, c, old, acc, bits);
+                    }
+                }
+            } else {
+                // every body is written: a body inactive here keeps its constant, except where the
+                // final rescale of the solids moves it by rounding (its state word then shows it)
+                int ids[NBMAX];
+#pragma unroll
+                for (int a = 0; a < NBMAX; ++a) ids[a] = a;
+                event = phase_node<NBMAX, NBMAX>(p, ids, zs, l, sg, hh, kin, mu, vterm, bodies, mask, dst, idx, u, c, old, acc, bits);
+            }
         } else if (c[0] < nx && c[1] < ny && c[2] < nz) {
             bits = pm << 1;  // a node of the tile outside the box: every phase is 0 there
         }
-        append_events(st, evlist, evcap, event);
-        // the state word of this wave's layer of the tile from the new phases
-        bits = wave_or(bits);
-        if (lane == 0) ((uint32_t *)tstate)[4 * tl + wave] = bits;
-        // one tile's loads at a time: letting the next tile's loads move up doubles the registers
-        asm volatile("" ::: "memory");
+        if (wave < 4) {
+            append_events(st, evlist, evcap, event);
+            // the state word of this wave's layer of the tile from the new phases
+            bits = wave_or(bits);
+            if (lane == 0) ((uint32_t *)tstate)[4 * tl + wave] = bits;
+        }
+        __syncthreads();  // the staged phases are free for the next tile
     }
-    acc.finish(nbod, st, cpart);
+    if (cfl) atomicOr(&st->err, 2u);  // rare: only when the input breaks the CFL bound
+    acc.finish(nbod, st, cpart, wave < 4);
 }
 
 // The rigid-body update of Sec. 3.1.1 (one block): the force partials of this step (momentum
@@ -547,7 +736,7 @@ __global__ __launch_bounds__(256) void k_tile_activity(Prm<T> p, int parity, Ste
         const uint4 w = tstate[t];
         return (w.x | w.y) | (w.z | w.w);
     };
-    const TileIter<T> ti(st->box[parity], p);
+    const TileIter<T> ti(st->tiles[parity], p);
     const uint32_t pm = pair_mask(p.nb);
     const int ntl = p.tn[0] * p.tn[1] * p.tn[2];
     // neighbour tile coordinate t + d (|d| <= 2) wrapped into [0, n) (n may be 1 or 2)

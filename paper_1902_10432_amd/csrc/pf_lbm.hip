@@ -359,48 +359,32 @@ template <typename T>
 void launch_phase_update(pf_lbm *h, const Prm<T> &p, int par, StepState *st, const BodyDev *bodies,
                          const double *sigma, const double *src, double *dst, cell_t *mask, ClassifyPart *cpart,
                          uint32_t *evlist, const uint32_t *tact, uint4 *tstate) {
-    dim3 g(h->cgrid), b(256);
+    const dim3 g(h->cgrid);
+#define PFL_PHASE(NB)                                                                                                \
+    k_phase_update<T, NB><<<g, dim3(phase_threads<NB>()), 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, \
+                                                                           evlist, h->ev_cap, tact, tstate)
     if (h->nb <= 1)
-        k_phase_update<T, 1><<<g, b, 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, evlist, h->ev_cap,
-                                                      tact, tstate);
+        PFL_PHASE(1);
     else if (h->nb <= 2)
-        k_phase_update<T, 2><<<g, b, 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, evlist, h->ev_cap,
-                                                      tact, tstate);
+        PFL_PHASE(2);
     else if (h->nb <= 4)
-        k_phase_update<T, 4><<<g, b, 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, evlist, h->ev_cap,
-                                                      tact, tstate);
+        PFL_PHASE(4);
     else if (h->nb <= 8)
-        k_phase_update<T, 8><<<g, b, 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, evlist, h->ev_cap,
-                                                      tact, tstate);
+        PFL_PHASE(8);
     else
-        k_phase_update<T, 16><<<g, b, 0, h->stream>>>(p, par, st, bodies, sigma, src, dst, mask, cpart, evlist, h->ev_cap,
-                                                      tact, tstate);
+        PFL_PHASE(16);
+#undef PFL_PHASE
 }
 
-// the three advection sweeps x (with the rigid-body update), y, z: a -> b -> a -> b
-template <typename T, int NBMAX>
-void launch_advect_n(pf_lbm *h, const Prm<T> &p, int par, StepState *st, const BodyDev *next, double *a, double *b,
-                     const uint32_t *tact) {
-    const dim3 g(h->box_grid), bl(256);
-    hipStream_t s = h->stream;
-    k_advect<T, 0, NBMAX><<<g, bl, 0, s>>>(p, par, st, next, a, b, tact);
-    k_advect<T, 1, NBMAX><<<g, bl, 0, s>>>(p, par, st, next, b, a, tact);
-    k_advect<T, 2, NBMAX><<<g, bl, 0, s>>>(p, par, st, next, a, b, tact);
-}
-
+// the x and y advection sweeps, a -> b (the z sweep is part of the phase update, b -> a)
 template <typename T>
-void launch_advect(pf_lbm *h, const Prm<T> &p, int par, StepState *st, const BodyDev *next, double *a, double *b,
+void launch_advect(pf_lbm *h, const Prm<T> &p, int par, StepState *st, const BodyDev *next, const double *a, double *b,
                    const uint32_t *tact) {
+    const dim3 g(h->box_grid), bl(XY_THREADS);
     if (h->nb <= 1)
-        launch_advect_n<T, 1>(h, p, par, st, next, a, b, tact);
-    else if (h->nb <= 2)
-        launch_advect_n<T, 2>(h, p, par, st, next, a, b, tact);
-    else if (h->nb <= 4)
-        launch_advect_n<T, 4>(h, p, par, st, next, a, b, tact);
-    else if (h->nb <= 8)
-        launch_advect_n<T, 8>(h, p, par, st, next, a, b, tact);
+        k_advect_xy<T, 1><<<g, bl, 0, h->stream>>>(p, par, st, next, a, b, tact);
     else
-        launch_advect_n<T, 16>(h, p, par, st, next, a, b, tact);
+        k_advect_xy<T, PF_LBM_MAX_BODIES><<<g, bl, 0, h->stream>>>(p, par, st, next, a, b, tact);
 }
 
 // one time step (Sec. 3): fluid, body forces + rigid update, phase fields, reclassification
@@ -451,7 +435,7 @@ int enqueue_step(pf_lbm *h, double *parts = nullptr) {
         // tile activity, and in its last block the rigid-body update from the force partials
         k_tile_activity<T><<<dim3(std::min(h->box_grid, 64) + 1), b, 0, s>>>(
             p, par, st, tstate, thot, tact, cur, next, pforce, fbk, (double *)(h->ws + h->L.hist), HIST_CAP);
-        // one kernel per sweep; the phase fields end in buffer A every step
+        // the phase fields end in buffer A every step
         launch_advect<T>(h, p, par, st, next, phiA, phiB, tact);
         launch_phase_update<T>(h, p, par, st, next, sigma, phiB, phiA, mask, cpart, evlist, tact, tstate);
         // conversion: usually returns at once (no node changed side), so a small grid
