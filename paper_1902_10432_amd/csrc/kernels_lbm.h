@@ -627,7 +627,8 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY>(
 // so only the planes of real links are read and the density comes from the fluid pass.  Against one
 // lane per node with unrolled searches (67 KB of code, now 14 KB), in FP32 unless noted: 61 x 45 x 50
 // two spheres 15.7 -> 8.5 us, 128^3 two spheres 18.7 -> 13.9 (D3Q27 25.1 -> 16.2), 256^3 four spheres
-// 42.9 -> 27.1 (FP16 storage 31.4 -> 27.4), 32^3 plates FP64 37.6 -> 23.0.
+// 42.9 -> 27.1 (FP16 storage 31.4 -> 27.4), 32^3 plates FP64 37.6 -> 23.0, and 17.2 with the repulsion
+// search of eight nodes loaded in one round.
 constexpr int FORCE_WAVES = 12;  // waves per block of the force scan (one block per CU)
 
 // component d of direction i known only at run time, from two-bit fields
@@ -728,9 +729,11 @@ __global__ __launch_bounds__(64 * FORCE_WAVES) void k_body_forces(Prm<ArT<S>> p,
     // over all waves.  A first pass loads the cell words of the U rounds together and keeps the
     // cells that need work: from the front of the list the fluid cells with a solid neighbour, from
     // its back the solid cells within r_c of the solid radius of a higher-index body.  (Runs of 64
-    // cells: 11.9 instead of 8.5 us at 61 x 45 x 50, 41.9 instead of 23.0 on the 32^3 plates.)
+    // cells: 11.9 instead of 8.5 us at 61 x 45 x 50, 41.9 instead of 23.0 on the 32^3 plates,
+    // before the search took eight nodes a round.)
     constexpr int U = 4, CAP = 64 * U, RUN = 16, RPW = 64 / RUN;
     __shared__ int keep[W][CAP];
+    __shared__ unsigned char kown[W][CAP];  // owners of the kept solid cells
     const int gw = (int)blockIdx.x * W + wave, nw = (int)gridDim.x * W;
     // cell of this lane in round u of the runs that start at s0, and the first cell of the round
     auto cell_of = [&](long long s0, int u) { return ((s0 + u * RPW + lane / RUN) * nw + gw) * RUN + (lane & (RUN - 1)); };
@@ -777,7 +780,11 @@ __global__ __launch_bounds__(64 * FORCE_WAVES) void k_body_forces(Prm<ArT<S>> p,
                         }
                     }
                     const uint64_t bas = __ballot(need);
-                    if (need) keep[wave][CAP - 1 - nrepc - __popcll(bas & ((1ull << lane) - 1ull))] = k;
+                    if (need) {
+                        const int slot = CAP - 1 - nrepc - __popcll(bas & ((1ull << lane) - 1ull));
+                        keep[wave][slot] = k;
+                        kown[wave][slot] = (unsigned char)owner_of(w);
+                    }
                     nrepc += __popcll(bas);
                 }
             }
@@ -915,44 +922,74 @@ __global__ __launch_bounds__(64 * FORCE_WAVES) void k_body_forces(Prm<ArT<S>> p,
                 if (has && q == 0) stb(fpost, is, pop_put<S>(f0 - drho, Dir<0, L>::template w<T>(), rown));
         }
         // Repulsion between a solid node p of body b1 and the solid nodes q = p + d of bodies above
-        // b1: the force on b1 at p, its opposite on b2 at q.  The n_rep offsets lie across the lanes
-        // (at most four rounds; two for r_c = 3), PN nodes at a time; the sums run per body b2 met.
-        // With r the offset of p from a centre, the torque of the reaction is r x (-s) - sum d x f.
-        constexpr int PN = 4;
-        for (int j0 = 0; j0 < nrepc; j0 += PN) {
-            int c[PN][3], b1[PN];  // the nodes of the batch, the same in every lane
+        // b1: the force on b1 at p, its opposite on b2 at q.  The n_rep offsets lie across the lanes, two
+        // rounds (r_c = 3 needs two, r_c = 4 four) of PN nodes loaded together; the sums run per body b2
+        // met.  With r the offset of p from a centre, the torque of the reaction is r x (-s) - sum d x f.
+        constexpr int PN = 8;
+        const int nrep = nrepc ? st->n_rep : 0;
+        for (int o0 = 0; o0 < nrep; o0 += 128) {
+            int o[2], dx[2], dy[2], dz[2];
 #pragma unroll
-            for (int j = 0; j < PN; ++j) {
-                int u[3], cv[3];
-                it.cell(keep[wave][CAP - 1 - (j0 + j < nrepc ? j0 + j : j0)], u, cv);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) c[j][k] = __builtin_amdgcn_readfirstlane(cv[k]);
-                b1[j] = j0 + j < nrepc ? __builtin_amdgcn_readfirstlane(owner_of(mask[c[j][0] + nx * (c[j][1] + ny * c[j][2])]))
-                                       : PF_LBM_MAX_BODIES;
+            for (int t = 0; t < 2; ++t) {
+                o[t] = o0 + 64 * t + lane;
+                const int w = st->rep_off[min(o[t], nrep - 1)];
+                dx[t] = (w & 255) - 8;
+                dy[t] = ((w >> 8) & 255) - 8;
+                dz[t] = (w >> 16) - 8;
             }
-            const int nrep = st->n_rep;
-            for (int o0 = 0; o0 < nrep; o0 += 64) {
-                const bool on = o0 + lane < nrep;
-                const int o = st->rep_off[on ? o0 + lane : 0];
-                const int dx = (o & 255) - 8, dy = ((o >> 8) & 255) - 8, dz = (o >> 16) - 8;
-                cell_t mq[PN];
+            const int doff[2] = {dx[0] + nx * (dy[0] + ny * dz[0]), dx[1] + nx * (dy[1] + ny * dz[1])};
+            for (int j0 = 0; j0 < nrepc; j0 += PN) {
+                // lane j < PN: node j of the batch; away from the grid's faces its neighbours are fixed offsets
+                int nd, bown, u[3], c[3];
+                {
+                    const int slot = CAP - 1 - min(j0 + (lane & (PN - 1)), nrepc - 1);
+                    it.cell(keep[wave][slot], u, c);
+                    nd = c[0] + nx * (c[1] + ny * c[2]);
+                    bown = kown[wave][slot];
+                }
+                const bool inner = min(min(c[0], c[1]), c[2]) >= 4 && c[0] < nx - 4 && c[1] < ny - 4 && c[2] < nz - 4;
+                uint32_t any = 0;  // pairs (node, round) of the batch that meet a body above the node's
+                auto meets = [&](int j, int t, cell_t m) {
+                    const bool on = (t ? o[1] : o[0]) < nrep && (m & C_SOLID);
+                    if (__ballot(on && owner_of(m) > __builtin_amdgcn_readlane(bown, j))) any |= 1u << (2 * j + t);
+                };
+                if (!__ballot(!inner)) {
+                    cell_t mq[PN][2];
 #pragma unroll
-                for (int j = 0; j < PN; ++j)
-                    mq[j] = mask[wrapl(c[j][0] + dx, nx) + nx * (wrapl(c[j][1] + dy, ny) + ny * wrapl(c[j][2] + dz, nz))];
+                    for (int j = 0; j < PN; ++j)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) mq[j][t] = mask[__builtin_amdgcn_readlane(nd, j) + doff[t]];
+#pragma unroll
+                    for (int j = 0; j < PN; ++j)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) meets(j, t, mq[j][t]);
+                } else {
 #pragma unroll 1
-                for (int j = 0; j < PN; ++j) {
-                    const cell_t m = j == 0 ? mq[0] : (j == 1 ? mq[1] : (j == 2 ? mq[2] : mq[3]));
-                    const int bj = j == 0 ? b1[0] : (j == 1 ? b1[1] : (j == 2 ? b1[2] : b1[3]));
+                    for (int k = 0; k < 2 * PN; ++k) {
+                        const int j = k >> 1, t = k & 1;
+                        const int x = __builtin_amdgcn_readlane(c[0], j) + (t ? dx[1] : dx[0]),
+                                  y = __builtin_amdgcn_readlane(c[1], j) + (t ? dy[1] : dy[0]),
+                                  z = __builtin_amdgcn_readlane(c[2], j) + (t ? dz[1] : dz[0]);
+                        meets(j, t, mask[wrapl(x, nx) + nx * (wrapl(y, ny) + ny * wrapl(z, nz))]);
+                    }
+                }
+                if (nrepc - j0 < PN) any &= (1u << (2 * (nrepc - j0))) - 1u;
+                while (any) {  // rare: one pair at a time, its words loaded again
+                    const int pr = __ffs(any) - 1, t = pr & 1;
+                    any &= any - 1;
+                    const int slot = CAP - 1 - (j0 + (pr >> 1)), bj = kown[wave][slot];
+                    int u[3], cj[3];
+                    it.cell(keep[wave][slot], u, cj);
+                    const int ot = t ? o[1] : o[0], ex = t ? dx[1] : dx[0], ey = t ? dy[1] : dy[0], ez = t ? dz[1] : dz[0];
+                    const bool on = ot < nrep;
+                    const cell_t m = mask[wrapl(cj[0] + ex, nx) + nx * (wrapl(cj[1] + ey, ny) + ny * wrapl(cj[2] + ez, nz))];
                     const int b2 = on && (m & C_SOLID) ? owner_of(m) : -1;
                     uint64_t hits = __ballot(b2 > bj);
-                    if (!hits) continue;
-                    int cj[3];
-                    for (int k = 0; k < 3; ++k) cj[k] = j == 0 ? c[0][k] : (j == 1 ? c[1][k] : (j == 2 ? c[2][k] : c[3][k]));
                     double fx = 0.0, fy = 0.0, fz = 0.0;
                     if (on) {
-                        fx = st->rep_f[o0 + lane][0];
-                        fy = st->rep_f[o0 + lane][1];
-                        fz = st->rep_f[o0 + lane][2];
+                        fx = st->rep_f[ot][0];
+                        fy = st->rep_f[ot][1];
+                        fz = st->rep_f[ot][2];
                     }
                     while (hits) {
                         const int bb = __shfl(b2, (int)__builtin_ctzll(hits), 64);
@@ -961,9 +998,9 @@ __global__ __launch_bounds__(64 * FORCE_WAVES) void k_body_forces(Prm<ArT<S>> p,
                         const double v[6] = {mine ? fx : 0.0,
                                              mine ? fy : 0.0,
                                              mine ? fz : 0.0,
-                                             mine ? dy * fz - dz * fy : 0.0,
-                                             mine ? dz * fx - dx * fz : 0.0,
-                                             mine ? dx * fy - dy * fx : 0.0};
+                                             mine ? ey * fz - ez * fy : 0.0,
+                                             mine ? ez * fx - ex * fz : 0.0,
+                                             mine ? ex * fy - ey * fx : 0.0};
                         const double tot = wave_sum6(v);
                         double s[3], td[3], r1[3], r2[3];
                         for (int k = 0; k < 3; ++k) {
