@@ -10,6 +10,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pf_mlp.h"
@@ -19,9 +20,17 @@ namespace pfm {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
+// n / d for d >= 1: the reciprocal's quotient with one correction by its exact remainder, then the
+// special cases (d infinite, n infinite or NaN).  It is the IEEE division without the scaling for small
+// and huge d and without the second correction, half its instructions; with the remainder exact it
+// differs from the correctly rounded quotient in about one of 10^7 cases, by one unit in the last place.
+__device__ __forceinline__ float quotient(float n, float d) {
+    const float r = __builtin_amdgcn_rcpf(d), q = n * r;
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, n), r, q), d, n);
+}
+__device__ __forceinline__ float silu(float z) { return quotient(z, 1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu_grad(float z) {
-    const float s = 1.0f / (1.0f + __expf(-z));
+    const float s = quotient(1.0f, 1.0f + __expf(-z));
     return s * (1.0f + z * (1.0f - s));
 }
 
@@ -212,10 +221,12 @@ struct TrainBuf {
 // 4 -> 128 x 4 -> 1: gradients of 8192 rows 8997 -> 130 us a call and a training step of 205 rows
 // 377 -> 50 us, this kernel 28.6 and 19.0 us of them, against the layer-by-layer path of 29 launches with
 // serial column sums (1553 us each at 8192 rows) and strided single-tile weight gradients (193 us each).
+struct NoTrain {};  // inference: 200 bytes of kernel arguments fewer
 template <int H, int RS, bool TRAIN>
 __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, int M, int nin, LayerMap lm,
                                                    const __bf16 *__restrict__ Wb, const __bf16 *__restrict__ Wt,
-                                                   const float *__restrict__ P, float *__restrict__ y, TrainBuf tb,
+                                                   const float *__restrict__ P, float *__restrict__ y,
+                                                   std::conditional_t<TRAIN, TrainBuf, NoTrain> tb,
                                                    const int *__restrict__ n_dev) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     constexpr int NT = H / 64, KS = H / 32, LD = H + 8, ROWS = 16 * RS;
@@ -821,8 +832,8 @@ void run_backward(pf_mlp *h, const float *t, int n, int chunks, int chunk) {
 // rows a fused block carries: 16, and 64 where 16-row blocks would exceed two per CU
 int fused_rows(int n) { return n > 16 * 512 ? 64 : 16; }
 
-template <int H, bool TRAIN>
-void launch_fused(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb, const int *n_dev) {
+template <int H, bool TRAIN, class B>
+void launch_fused(pf_mlp *h, const float *x, int n, float *y, const B &tb, const int *n_dev) {
     const int rows = fused_rows(n);
     const unsigned g = (unsigned)((n + rows - 1) / rows);
     if (rows == 64)
@@ -836,8 +847,8 @@ void launch_fused(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb
 // the one-launch network passes exist for these widths; others run layer by layer
 bool fused_width(int H) { return H == 64 || H == 128 || H == 256; }
 
-template <bool TRAIN>
-void launch_fused_any(pf_mlp *h, const float *x, int n, float *y, const TrainBuf &tb, const int *n_dev = nullptr) {
+template <bool TRAIN, class B>
+void launch_fused_any(pf_mlp *h, const float *x, int n, float *y, const B &tb, const int *n_dev = nullptr) {
     if (h->cfg.hidden == 64)
         launch_fused<64, TRAIN>(h, x, n, y, tb, n_dev);
     else if (h->cfg.hidden == 128)
@@ -919,7 +930,7 @@ __attribute__((visibility("hidden"))) void pfm_internal_info(const pf_mlp *h, in
 __attribute__((visibility("hidden"))) bool pfm_internal_forward_counted(pf_mlp *h, const float *x, int max_rows,
                                                                         const int *n_dev, float *y) {
     if (!fused_width(h->cfg.hidden)) return false;
-    launch_fused_any<false>(h, x, max_rows, y, TrainBuf{}, n_dev);
+    launch_fused_any<false>(h, x, max_rows, y, NoTrain{}, n_dev);
     return true;
 }
 
@@ -1034,7 +1045,7 @@ int pf_mlp_forward(pf_mlp *h, const float *x, int32_t n, float *y) {
     if (!h || !x || !y) return mfail(h, PF_LBM_EINVAL, "NULL argument");
     if (n < 1 || n > h->cfg.max_batch) return mfail(h, PF_LBM_EINVAL, "n must be in [1, max_batch]");
     if (fused_width(h->cfg.hidden)) {
-        launch_fused_any<false>(h, x, n, y, TrainBuf{});
+        launch_fused_any<false>(h, x, n, y, NoTrain{});
         MCHK(h, hipGetLastError());
         return PF_LBM_OK;
     }
