@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -130,7 +131,7 @@ Layout make_layout(long long Np, int nb, int prec, int q, int cpart_n, int force
     // D3Q27: one word of solid-neighbour bits per node (D3Q19 keeps them in the cell word)
     L.nbw = q == 27 ? take((size_t)Np * sizeof(uint32_t)) : 0;
     L.bodies = take(2 * sizeof(BodyDev) * std::max(nb, 1));  // current / next, by step parity
-    L.state = take(sizeof(StepState));
+    L.state = take(sizeof(StepState));                        // right after the tables (pf_lbm_forces)
     L.sigma = take(sizeof(double) * (nb + 1) * (nb + 1));
     L.pforce = take(sizeof(double) * force_grid * std::max(nb, 1) * 6);
     L.cpart = take(sizeof(ClassifyPart) * cpart_n);
@@ -813,13 +814,17 @@ int pf_lbm_step_noalloc(pf_lbm *h, int32_t n_steps) {
 
 int pf_lbm_forces(pf_lbm *h, double *F, double *T, double *X, double *V, double *W) {
     if (!h) return fail(nullptr, PF_LBM_EINVAL, "handle is NULL");
+    // one copy from the current body table to the error bits: the step state follows the tables
+    // (make_layout), and a second copy of a few bytes costs as much as the first
     std::vector<BodyDev> bd(std::max(h->nb, 1));
-    StepState st;
     const size_t tab = sizeof(BodyDev) * bd.size();
-    HIPCHK(h, hipMemcpyAsync(bd.data(), h->ws + h->L.bodies + (h->steps & 1) * tab, tab, hipMemcpyDeviceToHost,
-                             h->stream));
-    HIPCHK(h, hipMemcpyAsync(&st, h->ws + h->L.state, sizeof st, hipMemcpyDeviceToHost, h->stream));
+    const size_t from = h->L.bodies + (h->steps & 1) * tab, err_at = h->L.state + offsetof(StepState, err);
+    uint32_t err = 0;
+    std::vector<char> buf(err_at + sizeof err - from);
+    HIPCHK(h, hipMemcpyAsync(buf.data(), h->ws + from, buf.size(), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
+    std::memcpy((void *)bd.data(), buf.data(), tab);
+    std::memcpy(&err, buf.data() + (err_at - from), sizeof err);
     for (int a = 0; a < h->nb; ++a)
         for (int d = 0; d < 3; ++d) {
             if (F) F[3 * a + d] = bd[a].F[d];
@@ -828,8 +833,8 @@ int pf_lbm_forces(pf_lbm *h, double *F, double *T, double *X, double *V, double 
             if (V) V[3 * a + d] = bd[a].V[d];
             if (W) W[3 * a + d] = bd[a].W[d];
         }
-    if (st.err & 1u) return fail(h, PF_LBM_ENONFINITE, "non-finite body force or state");
-    if (st.err & 2u) return fail(h, PF_LBM_ENONFINITE, "advection velocity above one cell per step");
+    if (err & 1u) return fail(h, PF_LBM_ENONFINITE, "non-finite body force or state");
+    if (err & 2u) return fail(h, PF_LBM_ENONFINITE, "advection velocity above one cell per step");
     return PF_LBM_OK;
 }
 
@@ -904,15 +909,15 @@ int pf_lbm_force_history(pf_lbm *h, int32_t max_steps, double *out, int32_t *n_o
     const int n = (int)std::min<long long>(avail, max_steps);
     if (n_out) *n_out = n;
     if (n == 0) return PF_LBM_OK;
+    // the rows of the last n steps (0-based steps - n ..): one run of the ring, or its end and its
+    // beginning
     const size_t row = sizeof(double) * h->nb * 6;
-    std::vector<double> ring((size_t)HIST_CAP * h->nb * 6);
-    HIPCHK(h, hipMemcpyAsync(ring.data(), h->ws + h->L.hist, ring.size() * sizeof(double), hipMemcpyDeviceToHost,
-                             h->stream));
+    const int first = (int)((h->steps - n) % HIST_CAP), head = std::min(n, HIST_CAP - first);
+    const char *ring = h->ws + h->L.hist;
+    HIPCHK(h, hipMemcpyAsync(out, ring + first * row, head * row, hipMemcpyDeviceToHost, h->stream));
+    if (head < n)
+        HIPCHK(h, hipMemcpyAsync((char *)out + head * row, ring, (n - head) * row, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
-    for (int k = 0; k < n; ++k) {
-        const long long step = h->steps - n + k;  // 0-based index of the step
-        std::memcpy((char *)out + (size_t)k * row, (const char *)ring.data() + (size_t)(step % HIST_CAP) * row, row);
-    }
     return PF_LBM_OK;
 }
 
