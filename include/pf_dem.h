@@ -67,11 +67,13 @@ int pf_dem_init(const pf_dem_config *cfg, const double *radii, const double *x0,
                 void *workspace, size_t ws_bytes, void *hip_stream, pf_dem **out, size_t *ws_bytes_needed);
 
 /* Bridge list, network forces and per-sphere force sums at the current positions, no motion.
- * Synchronises once (to size the network's batch).  ENOMEM when a sphere has more than
+ * Synchronises at its end, where it reads the device's error bits (networks of a width other than 64,
+ * 128 or 256 also wait once to size their batch).  ENOMEM when a sphere has more than
  * max_neighbours partners or the run more than max_pairs bridges (the state is unchanged). */
 int pf_dem_evaluate(pf_dem *h);
 
-/* n_steps x (pf_dem_evaluate, then v += F / m dt, x += v dt, wrapped into the box). */
+/* n_steps x (pf_dem_evaluate, then v += F / m dt, x += v dt, wrapped into the box), waited for once, at
+ * the end; an error leaves the state of the last step that succeeded. */
 int pf_dem_step(pf_dem *h, int32_t n_steps);
 
 /* Current state, HOST arrays of [n][3] (any may be NULL): positions, velocities and the forces of

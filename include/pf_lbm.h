@@ -189,7 +189,7 @@ int pf_lbm_timing(pf_lbm *h, int32_t enable, double *out4);
 int pf_lbm_force_history(pf_lbm *h, int32_t max_steps, double *out, int32_t *n_out);
 
 /* Batched stepping of independent simulations (grids of any size): advances each of the n
- * handles by n_steps, launching step pairs round robin over the handles.  Each handle launches
+ * handles by n_steps, launching runs of steps round robin over the handles.  Each handle launches
  * on its own stream (given at pf_lbm_init), so the kernels of different instances overlap on the
  * GPU; per instance the result is bit for bit that of pf_lbm_step.  Handles must be distinct.
  * Returns the first error (its message on that handle). */
