@@ -1210,21 +1210,32 @@ __global__ void k_zero_mask(Prm<T> p, cell_t *mask) {
     for (int idx = blockIdx.x * 256 + threadIdx.x; idx < p.N; idx += gridDim.x * 256) mask[idx] = 0;
 }
 
+// read-out of a stored plane (a phase field, the pseudopotential): four nodes a thread, a block 1024
+// consecutive nodes.  Bound by memory: 12 B a node (FP64 -> FP32), 33 us at 256^3; 70 as part of k_fields,
+// which also read the cell word and took one node a thread.
+constexpr int COPY_NODES = 1024;
+template <typename T, typename D>
+__global__ __launch_bounds__(256) void k_copy_field(const T *__restrict__ src, D *__restrict__ dst, long long n) {
+    const long long i0 = (long long)blockIdx.x * COPY_NODES + threadIdx.x;
+    T v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = src[min(i0 + 256 * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i0 + 256 * u < n) dst[i0 + 256 * u] = (D)v[u];
+}
+
 template <typename S, typename D, class L>
 __global__ void k_fields(Prm<ArT<S>> p, int which, const S *__restrict__ f, const cell_t *__restrict__ mask,
-                         const ArT<S> *__restrict__ psi, const double *__restrict__ phi, D *__restrict__ dst) {
+                         const ArT<S> *__restrict__ psi, D *__restrict__ dst) {
     using T = ArT<S>;
     for (int idx = blockIdx.x * 256 + threadIdx.x; idx < p.N; idx += gridDim.x * 256) {
         const cell_t m = mask[idx];
         double out = 0.0;
-        if (which >= 16) {
-            out = phi[(long long)(which - 16) * p.Np + idx];
-        } else if (which == 4) {
+        if (which == 4) {
             out = (m & C_SOLID) ? 1.0 : 0.0;
         } else if (which == 5) {
             out = (m & C_SOLID) ? (double)owner_of(m) : -1.0;
-        } else if (which == 6) {
-            out = (double)psi[idx];
         } else if (!(m & C_SOLID)) {
             const T rr = sizeof(S) == 2 ? ref_density(psi[idx], p.rho0) : T(0);
             double s = 0.0;

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pf_lbm.h"
@@ -512,10 +513,20 @@ void launch_fields(pf_lbm *h, int which, int par, void *dst, int dst_dtype) {
     // pseudopotential of the last step taken (before the first step: that of the initial state)
     const T *psi = (const T *)(h->ws + (par ? h->L.psi : h->L.psiB));
     const double *phi = (const double *)(h->ws + h->L.phiA);
+    auto launch = [&](auto *out) {
+        using D = std::remove_pointer_t<decltype(out)>;
+        const unsigned gc = (unsigned)(((long long)h->N + COPY_NODES - 1) / COPY_NODES);
+        if (which >= PF_LBM_FIELD_PHI)
+            k_copy_field<double, D><<<gc, b, 0, h->stream>>>(phi + (size_t)(which - PF_LBM_FIELD_PHI) * h->Np, out, h->N);
+        else if (which == PF_LBM_FIELD_PSI)
+            k_copy_field<T, D><<<gc, b, 0, h->stream>>>(psi, out, h->N);
+        else
+            k_fields<S, D, Lat><<<g, b, 0, h->stream>>>(p, which, f, mask, psi, out);
+    };
     if (dst_dtype == PF_LBM_DST_F64)
-        k_fields<S, double, Lat><<<g, b, 0, h->stream>>>(p, which, f, mask, psi, phi, (double *)dst);
+        launch((double *)dst);
     else
-        k_fields<S, float, Lat><<<g, b, 0, h->stream>>>(p, which, f, mask, psi, phi, (float *)dst);
+        launch((float *)dst);
 }
 
 }  // namespace
