@@ -737,9 +737,19 @@ int static_parts(pf_lbm *h, double **out) {
 
 constexpr int GRAPH_STEPS[2] = {2, 32};
 
+// an executable graph is destroyed only once its replays, queued on stream s, are over: the runtime may
+// still be reading it while they run.  (On a stream that the caller is capturing nothing can be waited
+// for; replays before the capture are then the caller's to have waited for.)
+void destroy_graph(hipGraphExec_t g, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) (void)hipStreamSynchronize(s);
+    (void)hipGetLastError();
+    (void)hipGraphExecDestroy(g);
+}
+
 void drop_graphs(pf_lbm *h) {
     for (hipGraphExec_t &g : h->graph) {
-        if (g) (void)hipGraphExecDestroy(g);
+        if (g) destroy_graph(g, h->stream);
         g = nullptr;
     }
     h->graph_failed = false;
@@ -960,6 +970,7 @@ int pf_lbm_step_batch(pf_lbm *const *handles, int32_t n, int32_t n_steps) {
 struct pf_lbm_batch {
     std::vector<pf_lbm *> hs;
     int graph_steps = 2;
+    hipStream_t stream = nullptr;         // the first instance's, on which the graph is replayed
     hipGraphExec_t graph = nullptr;
     std::vector<int> parity;              // step parity of each instance at capture
     std::vector<unsigned> gen;            // launch-shape generation of each instance at capture
@@ -982,9 +993,9 @@ int bfail(pf_lbm_batch *b, int code, const std::string &msg) {
 
 // capture graph_steps steps of every instance into one executable graph
 int batch_capture(pf_lbm_batch *b) {
-    if (b->graph) (void)hipGraphExecDestroy(b->graph);
-    b->graph = nullptr;
     hipStream_t origin = b->hs[0]->stream;
+    if (b->graph) destroy_graph(b->graph, origin);
+    b->graph = nullptr;
     const int n = (int)b->hs.size();
     std::vector<long long> s0(n);
     for (int i = 0; i < n; ++i) s0[i] = b->hs[i]->steps;
@@ -1037,6 +1048,7 @@ int pf_lbm_batch_create(pf_lbm *const *handles, int32_t n, int32_t graph_steps, 
     pf_lbm_batch *b = new (std::nothrow) pf_lbm_batch();
     if (!b) return fail(nullptr, PF_LBM_ENOMEM, "host allocation failed");
     b->hs.assign(handles, handles + n);
+    b->stream = handles[0]->stream;
     b->graph_steps = graph_steps;
     b->parity.assign(n, -1);
     b->gen.assign(n, 0u);
@@ -1090,7 +1102,7 @@ int pf_lbm_batch_step(pf_lbm_batch *b, int32_t n_steps) {
 
 void pf_lbm_batch_destroy(pf_lbm_batch *b) {
     if (!b) return;
-    if (b->graph) (void)hipGraphExecDestroy(b->graph);
+    if (b->graph) destroy_graph(b->graph, b->stream);
     for (hipEvent_t e : b->ev)
         if (e) (void)hipEventDestroy(e);
     delete b;
