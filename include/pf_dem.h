@@ -73,7 +73,8 @@ int pf_dem_init(const pf_dem_config *cfg, const double *radii, const double *x0,
 int pf_dem_evaluate(pf_dem *h);
 
 /* n_steps x (pf_dem_evaluate, then v += F / m dt, x += v dt, wrapped into the box), waited for once, at
- * the end; an error leaves the state of the last step that succeeded. */
+ * the end; an error leaves the state of the last step that succeeded.  Both calls are refused (EDEVICE,
+ * nothing enqueued) while the stream is being captured. */
 int pf_dem_step(pf_dem *h, int32_t n_steps);
 
 /* Current state, HOST arrays of [n][3] (any may be NULL): positions, velocities and the forces of

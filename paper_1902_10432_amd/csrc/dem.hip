@@ -584,6 +584,12 @@ int enqueue_evaluation(pf_dem *h, bool move) {
 
 // n evaluations with motion, or one without (n < 0); one wait, at the end
 int run_evaluations(pf_dem *h, int n) {
+    // refused before anything is enqueued where the wait at the end would be: the steps exchange the
+    // state's two buffers as they are enqueued, and captured ones do not run
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    DCHK(h, hipStreamIsCapturing(h->stream, &cap));
+    if (cap != hipStreamCaptureStatusNone)
+        return dfail(h, PF_LBM_EDEVICE, "the run waits for its stream, which is being captured");
     DCHK(h, hipMemsetAsync(h->d.ctl + 1, 0, 4, h->stream));
     for (int s = 0; s < std::max(n, 1); ++s) {
         const int rc = enqueue_evaluation(h, n > 0);
