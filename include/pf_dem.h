@@ -81,7 +81,7 @@ int pf_dem_step(pf_dem *h, int32_t n_steps);
  * the last evaluation.  Synchronises. */
 int pf_dem_state(pf_dem *h, double *x, double *v, double *f);
 
-/* Bridges of the last evaluation, ordered by (i, j), i < j: ij [k][2], features [k][4] (the
+/* Bridges of the last evaluation that succeeded, ordered by (i, j), i < j: ij [k][2], features [k][4] (the
  * unnormalised network features above), force [k] (the force F used, override included).
  * HOST arrays of max_out rows; *n_out receives the number of bridges (rows beyond max_out are not
  * written).  Synchronises. */

@@ -45,12 +45,14 @@ struct DemDev {
     int nc;               // cells per edge of the search grid, 0: every pair is tested
     int *cell;            // cell of each sphere
     int *cstart, *cidx;   // first slot of each cell (nc^3 + 1), sphere of each slot
+    // two bridge lists of max_pairs rows: the rows of an evaluation go to the one that ctl[3] does not name
     int *pij;
     double *pfeat, *pforce;
     float *X;
     const float *Y;
     // [0] bridges of the current evaluation, [1] error bits (1: neighbours, 2: pairs; once set, the
-    // steps that follow change nothing), [2] bridges of the last evaluation without an error
+    // steps that follow change nothing), [2] bridges of the last evaluation without an error and [3] its
+    // list (0 or 1)
     int *ctl;
     const int *over_ij;
     const double *over_f;
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(256) void k_dem_rows(DemDev p) {
     const int i = i0 + (tid >> 2);
     if (i >= p.n) return;
     const double xi = p.x[3 * i], yi = p.x[3 * i + 1], zi = p.x[3 * i + 2], Ri = p.R[i];
-    const int deg = p.deg[i], lower = deg - p.nup[i];
+    const int deg = p.deg[i], lower = deg - p.nup[i], list = p.ctl[3] ^ 1;
     for (int k = max(lower, 0) + (tid & 3); k < deg; k += 4) {
         const int j = p.nbr[(long long)i * p.cap + k];
         const int row = offs[tid >> 2] + (k - lower);
@@ -280,23 +282,27 @@ __global__ __launch_bounds__(256) void k_dem_rows(DemDev p) {
         const double gap = sqrt(dx * dx + dy * dy + dz * dz) - (Ri + p.R[j]);
         double f[4], rs;
         bridge_features(p, Ri, p.R[j], gap, f, &rs);
-        p.pij[2 * row] = i;
-        p.pij[2 * row + 1] = j;
+        const int out = row + list * p.max_pairs;
+        p.pij[2 * out] = i;
+        p.pij[2 * out + 1] = j;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            p.pfeat[4 * (long long)row + c] = f[c];
+            p.pfeat[4 * (long long)out + c] = f[c];
             p.X[4 * (long long)row + c] = (float)((f[c] - (double)p.ish[c]) * (double)p.isc[c]);
         }
     }
 }
 
 // Forces, sixteen lanes per sphere (one partner each, then the next sixteen), summed in partner order;
-// with move != 0 the Euler step into the other state buffer.  After an error the state is carried over
-// unchanged and nothing else is written.
+// with move != 0 the Euler step into the other state buffer.  The evaluation's bridge list becomes the
+// current one.  After an error the state is carried over unchanged and nothing else is written.
 __global__ __launch_bounds__(256) void k_dem_forces(DemDev p, int move) {
     const int i = blockIdx.x * 16 + (threadIdx.x >> 4), q = threadIdx.x & 15;
     const bool err = p.ctl[1] != 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && !err) p.ctl[2] = p.ctl[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !err) {
+        p.ctl[2] = p.ctl[0];
+        p.ctl[3] ^= 1;
+    }
     const bool in = i < p.n;
     const int is = in ? i : 0;
     const double xi = p.x[3 * is], yi = p.x[3 * is + 1], zi = p.x[3 * is + 2], Ri = p.R[is];
@@ -389,7 +395,7 @@ struct pf_dem {
     char *ws = nullptr;
     DemDev d{};
     int *ctl_host = nullptr;  // pinned, 4 ints
-    int last_pairs = 0;
+    int last_pairs = 0, last_list = 0;  // bridges of the last evaluation without an error, and its list
     std::string err;
 };
 
@@ -448,8 +454,8 @@ int pf_dem_init(const pf_dem_config *cfg, const double *radii, const double *x0,
                  ox2 = take(24 * (size_t)n), ov2 = take(24 * (size_t)n), ocst = take(4 * (size_t)(MAX_NC * MAX_NC * MAX_NC + 1)),
                  ocidx = take(4 * (size_t)n), ocell = take(4 * (size_t)n),
                  oF = take(24 * (size_t)n), onbr = take(4 * (size_t)n * cap), odeg = take(4 * (size_t)n),
-                 onup = take(4 * (size_t)n), ooff = take(4 * (size_t)n), opij = take(8 * (size_t)P),
-                 opfeat = take(32 * (size_t)P), opforce = take(8 * (size_t)P), oX = take(16 * (size_t)P),
+                 onup = take(4 * (size_t)n), ooff = take(4 * (size_t)n), opij = take(16 * (size_t)P),
+                 opfeat = take(64 * (size_t)P), opforce = take(8 * (size_t)P), oX = take(16 * (size_t)P),
                  oY = take(4 * (size_t)P), octl = take(16), oover = take(8 * MAX_OVERRIDES),
                  overf = take(8 * MAX_OVERRIDES);
     if (ws_bytes_needed) *ws_bytes_needed = off;
@@ -591,13 +597,14 @@ int run_evaluations(pf_dem *h, int n) {
     if (cap != hipStreamCaptureStatusNone)
         return dfail(h, PF_LBM_EDEVICE, "the run waits for its stream, which is being captured");
     DCHK(h, hipMemsetAsync(h->d.ctl + 1, 0, 4, h->stream));
-    for (int s = 0; s < std::max(n, 1); ++s) {
-        const int rc = enqueue_evaluation(h, n > 0);
-        if (rc != PF_LBM_OK) return rc;
-    }
+    int rc = PF_LBM_OK;
+    for (int s = 0; s < std::max(n, 1) && rc == PF_LBM_OK; ++s) rc = enqueue_evaluation(h, n > 0);
+    // also where a step could not be enqueued: those before it have exchanged the lists
     DCHK(h, hipMemcpyAsync(h->ctl_host, h->d.ctl, 16, hipMemcpyDeviceToHost, h->stream));
     DCHK(h, hipStreamSynchronize(h->stream));
     h->last_pairs = h->ctl_host[2];
+    h->last_list = h->ctl_host[3];
+    if (rc != PF_LBM_OK) return rc;
     if (h->ctl_host[1] & 1) return dfail(h, PF_LBM_ENOMEM, "a sphere has more than max_neighbours bridged partners");
     if (h->ctl_host[1] & 2)
         return dfail(h, PF_LBM_ENOMEM, "%d bridges exceed max_pairs %d", h->ctl_host[0], h->d.max_pairs);
@@ -635,8 +642,10 @@ int pf_dem_pairs(pf_dem *h, int32_t max_out, int32_t *ij, double *features, doub
     const int k = std::min(max_out, h->last_pairs);
     *n_out = h->last_pairs;
     if (k > 0) {
-        if (ij) DCHK(h, hipMemcpyAsync(ij, h->d.pij, 8 * (size_t)k, hipMemcpyDeviceToHost, h->stream));
-        if (features) DCHK(h, hipMemcpyAsync(features, h->d.pfeat, 32 * (size_t)k, hipMemcpyDeviceToHost, h->stream));
+        const size_t row0 = (size_t)h->last_list * h->d.max_pairs;
+        if (ij) DCHK(h, hipMemcpyAsync(ij, h->d.pij + 2 * row0, 8 * (size_t)k, hipMemcpyDeviceToHost, h->stream));
+        if (features)
+            DCHK(h, hipMemcpyAsync(features, h->d.pfeat + 4 * row0, 32 * (size_t)k, hipMemcpyDeviceToHost, h->stream));
         if (force) DCHK(h, hipMemcpyAsync(force, h->d.pforce, 8 * (size_t)k, hipMemcpyDeviceToHost, h->stream));
     }
     DCHK(h, hipStreamSynchronize(h->stream));

@@ -53,3 +53,41 @@ def test_captured_stream_is_refused(hidden):
     ref.step(2)
     for a, b in zip(_state(run), _state(ref)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("cap,max_pairs,match", [(1, 256, "max_neighbours"), (8, 3, "max_pairs")])
+def test_overflow_keeps_the_bridge_list(cap, max_pairs, match):
+    """A sphere of the lowest index flies at one of three bridged pairs: the evaluation that finds the
+    fourth bridge, ahead of the others in the list, overflows.  Pairs, features and forces are then
+    those of the evaluation before it, also when the run goes on for an even or odd number of steps."""
+    from paper_1902_10432_amd.surrogate import SurrogateError
+    print(f"case overflow cap={cap} max_pairs={max_pairs}", flush=True)
+    L, R = 80.0, np.array([2.0, 2.1, 2.2, 2.3, 2.4, 2.5, 2.6])
+    x = np.array([[20.0, 31.0, 20.0], [20.0, 20.0, 20.0], [25.0, 20.0, 20.0], [50.0, 20.0, 20.0], [55.2, 20.0, 20.0],
+                  [50.0, 60.0, 20.0], [50.0, 65.8, 20.0]])
+    v = np.zeros((7, 3))
+    v[0, 1], v[1, 0], v[3, 0], v[5, 1] = -1.0, 0.003, -0.004, 0.005  # the features change every step
+    ref, good = _run(L, R, x, v, 8), 0
+    while True:  # steps until the evaluation at the reached positions finds the fourth bridge
+        ref.evaluate()
+        if len(ref.pairs()["ij"]) > 3:
+            break
+        ref.step(1)
+        good += 1
+    assert 2 <= good < 20
+    ref = _run(L, R, x, v, 8)
+    ref.step(good)
+    want, state = ref.pairs(), _state(ref)
+    assert len(want["ij"]) == 3
+    for extra in (1, 2, 5):
+        run = _run(L, R, x, v, cap, max_pairs)
+        with pytest.raises(SurrogateError, match=match):
+            run.step(good + extra)
+        for a, b in zip(_state(run), state):
+            assert np.array_equal(a, b)
+        for _ in range(2):
+            got = run.pairs()
+            for k in ("ij", "features", "force"):
+                assert np.array_equal(got[k], want[k]), k
+            with pytest.raises(SurrogateError, match=match):
+                run.evaluate()
