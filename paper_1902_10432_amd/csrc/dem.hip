@@ -67,8 +67,13 @@ constexpr int MAX_NC = 16;
 // spheres from which the cell grid is used
 constexpr int CELL_MIN_N = 2048;
 
-// cell coordinate of x in [0, L)
-__device__ __forceinline__ int cell_of(double x, double scale, int nc) { return min(nc - 1, max(0, (int)(x * scale))); }
+// cell coordinate of x, in [0, L) unless the sphere moved so far (more than 2^53 boxes) in the step that
+// the wrap rounded: then that of its image in the box, which its minimum images belong to
+__device__ __forceinline__ int cell_of(double x, double scale, int nc) {
+    double t = x * scale;
+    if (!(t >= 0.0 && t < nc)) t -= nc * floor(t / nc);
+    return min(nc - 1, max(0, (int)t));
+}
 
 // index of the cell of a sphere at x, y, z
 __device__ __forceinline__ int cell_index(double x, double y, double z, double scale, int nc) {
