@@ -49,7 +49,8 @@ int32_t pf_mlp_num_params(const pf_mlp *h);
 int pf_mlp_set_params(pf_mlp *h, const float *params);
 int pf_mlp_get_params(pf_mlp *h, float *params);
 
-/* Forward pass: x DEVICE [n][n_in] FP32 -> y DEVICE [n] FP32, 1 <= n <= max_batch.  Async. */
+/* Forward pass: x DEVICE [n][n_in] FP32 -> y DEVICE [n] FP32 (which may lie over x), 1 <= n <= max_batch.
+ * Async. */
 int pf_mlp_forward(pf_mlp *h, const float *x, int32_t n, float *y);
 
 /* Mean-squared-error loss over the batch and its gradient with respect to every parameter:

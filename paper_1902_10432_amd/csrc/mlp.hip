@@ -1063,7 +1063,11 @@ int pf_mlp_get_params(pf_mlp *h, float *params) {
 int pf_mlp_forward(pf_mlp *h, const float *x, int32_t n, float *y) {
     if (!h || !x || !y) return mfail(h, PF_LBM_EINVAL, "NULL argument");
     if (n < 1 || n > h->cfg.max_batch) return mfail(h, PF_LBM_EINVAL, "n must be in [1, max_batch]");
-    if (fused_width(h->cfg.hidden)) {
+    // the one-launch pass reads inputs while other blocks write outputs; the layer-by-layer path copies the
+    // inputs first, so outputs may lie over them
+    const uintptr_t x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+    const bool apart = y0 + sizeof(float) * (size_t)n <= x0 || x0 + sizeof(float) * (size_t)n * h->cfg.n_in <= y0;
+    if (fused_width(h->cfg.hidden) && apart) {
         launch_fused_any<false>(h, x, n, y, NoTrain{});
         MCHK(h, hipGetLastError());
         return PF_LBM_OK;
