@@ -208,6 +208,7 @@ int pf_lbm_step_batch(pf_lbm *const *handles, int32_t n, int32_t n_steps);
 typedef struct pf_lbm_batch pf_lbm_batch;
 int pf_lbm_batch_create(pf_lbm *const *handles, int32_t n, int32_t graph_steps, pf_lbm_batch **out);
 int pf_lbm_batch_step(pf_lbm_batch *b, int32_t n_steps);
+/* Waits for the replays still queued; touches neither the handles nor their streams. */
 void pf_lbm_batch_destroy(pf_lbm_batch *b);
 const char *pf_lbm_batch_last_error(const pf_lbm_batch *b);
 
@@ -231,7 +232,10 @@ int pf_lbm_set_tile(pf_lbm *h, int32_t rows, int32_t planes);
  * path on purpose (tests).  Errors: PF_LBM_EINVAL (out of range or NULL handle). */
 int pf_lbm_set_event_capacity(pf_lbm *h, int32_t entries);
 
-/* Release the handle (the workspace stays the caller's).  NULL is ignored. */
+/* Release the handle (the workspace stays the caller's).  NULL is ignored.  Waits for captured steps that
+ * may still be queued on the handle's stream; the stream may be destroyed first once a call that
+ * synchronises it (pf_lbm_forces, pf_lbm_diagnostics, pf_lbm_force_history) has followed the last
+ * step. */
 void pf_lbm_destroy(pf_lbm *h);
 
 /* Message of the last failure on h (or of the last failed pf_lbm_init when h is NULL). */

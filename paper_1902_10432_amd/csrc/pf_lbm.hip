@@ -83,6 +83,7 @@ struct pf_lbm {
     // spreads the launch gap between replays over more steps)
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     bool graph_failed = false;
+    bool replays_queued = false;  // replays since the handle last waited for its stream
 };
 
 namespace {
@@ -716,6 +717,13 @@ int eager_step(pf_lbm *h, double *parts = nullptr) {
                                     : enqueue_step<half_t, D3Q19>(h, parts);
 }
 
+// wait for the handle's stream
+hipError_t wait_stream(pf_lbm *h) {
+    const hipError_t e = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) h->replays_queued = false;
+    return e;
+}
+
 // Device address of this GPU's copy of the static force partials, looked up once per device
 // (with that device current) and kept.
 std::mutex g_static_mu;
@@ -740,16 +748,19 @@ constexpr int GRAPH_STEPS[2] = {2, 32};
 // an executable graph is destroyed only once its replays, queued on stream s, are over: the runtime may
 // still be reading it while they run.  (On a stream that the caller is capturing nothing can be waited
 // for; replays before the capture are then the caller's to have waited for.)
-void destroy_graph(hipGraphExec_t g, hipStream_t s) {
+void wait_replays(hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) (void)hipStreamSynchronize(s);
     (void)hipGetLastError();
-    (void)hipGraphExecDestroy(g);
 }
 
+// Drops the captured steps.  The stream is touched only where replays may still be queued: after a read-out
+// that waited for them the caller may have destroyed it.
 void drop_graphs(pf_lbm *h) {
+    if (h->replays_queued) wait_replays(h->stream);
+    h->replays_queued = false;
     for (hipGraphExec_t &g : h->graph) {
-        if (g) destroy_graph(g, h->stream);
+        if (g) (void)hipGraphExecDestroy(g);
         g = nullptr;
     }
     h->graph_failed = false;
@@ -803,6 +814,7 @@ int pf_lbm_step(pf_lbm *h, int32_t n_steps) {
     for (int k = 1; k >= 0; --k) {
         while (n >= GRAPH_STEPS[k] && !h->timing && ensure_graph(h, k)) {
             HIPCHK(h, hipGraphLaunch(h->graph[k], h->stream));
+            h->replays_queued = true;
             h->steps += GRAPH_STEPS[k];
             n -= GRAPH_STEPS[k];
         }
@@ -843,7 +855,7 @@ int pf_lbm_forces(pf_lbm *h, double *F, double *T, double *X, double *V, double 
     uint32_t err = 0;
     std::vector<char> buf(err_at + sizeof err - from);
     HIPCHK(h, hipMemcpyAsync(buf.data(), h->ws + from, buf.size(), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+    HIPCHK(h, wait_stream(h));
     std::memcpy((void *)bd.data(), buf.data(), tab);
     std::memcpy(&err, buf.data() + (err_at - from), sizeof err);
     for (int a = 0; a < h->nb; ++a)
@@ -889,7 +901,7 @@ int pf_lbm_diagnostics(pf_lbm *h, double *out4) {
     if (!h || !out4) return fail(h, PF_LBM_EINVAL, "handle or output is NULL");
     StepState st;
     HIPCHK(h, hipMemcpyAsync(&st, h->ws + h->L.state, sizeof st, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+    HIPCHK(h, wait_stream(h));
     out4[0] = (double)h->steps;
     out4[1] = (double)st.n_f2s;
     out4[2] = (double)st.n_s2f;
@@ -904,7 +916,7 @@ int pf_lbm_timing(pf_lbm *h, int32_t enable, double *out4) {
         h->timed = 0;
         return PF_LBM_OK;
     }
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+    HIPCHK(h, wait_stream(h));
     double kern = 0.0, step = 0.0;
     for (int k = 0; k < h->timed; ++k) {
         float a = 0.f, b = 0.f;
@@ -938,7 +950,7 @@ int pf_lbm_force_history(pf_lbm *h, int32_t max_steps, double *out, int32_t *n_o
     HIPCHK(h, hipMemcpyAsync(out, ring + first * row, head * row, hipMemcpyDeviceToHost, h->stream));
     if (head < n)
         HIPCHK(h, hipMemcpyAsync((char *)out + head * row, ring, (n - head) * row, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+    HIPCHK(h, wait_stream(h));
     return PF_LBM_OK;
 }
 
@@ -970,7 +982,6 @@ int pf_lbm_step_batch(pf_lbm *const *handles, int32_t n, int32_t n_steps) {
 struct pf_lbm_batch {
     std::vector<pf_lbm *> hs;
     int graph_steps = 2;
-    hipStream_t stream = nullptr;         // the first instance's, on which the graph is replayed
     hipGraphExec_t graph = nullptr;
     std::vector<int> parity;              // step parity of each instance at capture
     std::vector<unsigned> gen;            // launch-shape generation of each instance at capture
@@ -994,7 +1005,10 @@ int bfail(pf_lbm_batch *b, int code, const std::string &msg) {
 // capture graph_steps steps of every instance into one executable graph
 int batch_capture(pf_lbm_batch *b) {
     hipStream_t origin = b->hs[0]->stream;
-    if (b->graph) destroy_graph(b->graph, origin);
+    if (b->graph) {
+        wait_replays(origin);
+        (void)hipGraphExecDestroy(b->graph);
+    }
     b->graph = nullptr;
     const int n = (int)b->hs.size();
     std::vector<long long> s0(n);
@@ -1048,7 +1062,6 @@ int pf_lbm_batch_create(pf_lbm *const *handles, int32_t n, int32_t graph_steps, 
     pf_lbm_batch *b = new (std::nothrow) pf_lbm_batch();
     if (!b) return fail(nullptr, PF_LBM_ENOMEM, "host allocation failed");
     b->hs.assign(handles, handles + n);
-    b->stream = handles[0]->stream;
     b->graph_steps = graph_steps;
     b->parity.assign(n, -1);
     b->gen.assign(n, 0u);
@@ -1102,7 +1115,12 @@ int pf_lbm_batch_step(pf_lbm_batch *b, int32_t n_steps) {
 
 void pf_lbm_batch_destroy(pf_lbm_batch *b) {
     if (!b) return;
-    if (b->graph) destroy_graph(b->graph, b->stream);
+    // the first event follows the last replay (the handles and their streams may be gone)
+    if (b->graph) {
+        (void)hipEventSynchronize(b->ev[0]);
+        (void)hipGetLastError();
+        (void)hipGraphExecDestroy(b->graph);
+    }
     for (hipEvent_t e : b->ev)
         if (e) (void)hipEventDestroy(e);
     delete b;
