@@ -502,6 +502,13 @@ template <int NBMAX>
 constexpr int phase_min_waves() {
     return NBMAX <= 2 ? 4 : (NBMAX <= 4 ? 3 : 1);
 }
+// blocks that share a CU (four SIMDs)
+template <int NBMAX>
+constexpr int phase_blocks_per_cu() {
+    return 4 * phase_min_waves<NBMAX>() / (phase_threads<NBMAX>() / 64);
+}
+static_assert(phase_blocks_per_cu<1>() == 2 && phase_blocks_per_cu<2>() == 2 && phase_blocks_per_cu<4>() == 3,
+              "grid of the phase update: one round of blocks");
 
 template <typename PT, int NBMAX>
 __global__ __launch_bounds__((phase_threads<NBMAX>()), (phase_min_waves<NBMAX>())) void k_phase_update(Prm<PT> p, int parity, StepState *st,

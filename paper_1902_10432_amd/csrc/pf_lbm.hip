@@ -605,12 +605,15 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
     const int box_blocks = (int)std::max(1LL, std::min(4096LL, (3 * vol0 / 2 + 255) / 256));
     const int box_grid = box_blocks;
     const int force_grid = std::min((box_blocks + 3) / 4, FORCE_GRID_MAX);
-    // phase update (and the classification partials it leaves): grid-stride over the tiles.  With
-    // up to 4 bodies and a box above 2^19 cells, three 4-wave blocks per CU, as many as a CU holds
-    // at that variant's registers, in one round (four per CU ran a second round and were no
-    // faster); otherwise two blocks per CU, four for boxes above 2^20 cells.  Each block's partials
-    // are summed at the start of the next step, so more blocks cost there.
-    const int cgrid = std::min(box_blocks, (n_bodies <= 4 && vol0 > (1LL << 19)) ? 768
+    // phase update (and the classification partials it leaves): grid-stride over the tiles.  With up to
+    // 4 bodies and a box above 2^19 cells, as many blocks as the card holds at that variant's registers,
+    // in one round (with a second round of half the blocks: two spheres at 200^3 46.2 instead of 38.9 us, one
+    // at 160^3 52.4 instead of 44.6); otherwise two blocks per CU, four for boxes above 2^20 cells.  Each
+    // block's partials are summed at the start of the next step, so more blocks cost there.
+    const int round = 256 * (n_bodies <= 1   ? phase_blocks_per_cu<1>()
+                             : n_bodies <= 2 ? phase_blocks_per_cu<2>()
+                                             : phase_blocks_per_cu<4>());
+    const int cgrid = std::min(box_blocks, (n_bodies <= 4 && vol0 > (1LL << 19)) ? round
                                            : (vol0 > (1LL << 20) ? 1024 : 512));
     const long long ntiles = (long long)((cfg->nx + TLX - 1) / TLX) * ((cfg->ny + TLY - 1) / TLY) * ((cfg->nz + TLZ - 1) / TLZ);
     const Layout L = make_layout(Np, n_bodies, cfg->precision, cfg->lattice, std::max(cgrid, box_grid), force_grid,
