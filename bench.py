@@ -217,7 +217,7 @@ def batched_sweep(args) -> int:
     tiles = None
     if not args.no_autotune:
         tiles = [s.autotune(4) for s in sims]
-        log("autotuned tiles: " + json.dumps(sorted({(t["tile_rows"], t["chunk_planes"]) for t in tiles})))
+        log("fastest tiles of the tuner (the default stays where it was faster): " + json.dumps(sorted({(t["tile_rows"], t["chunk_planes"]) for t in tiles})))
     graph = Batch(sims, graph_steps=args.graph_steps)
     # warm-up of every path (each captures its graphs)
     step_batch(sims, 2)
@@ -374,7 +374,7 @@ def tune_tile(sim, args, precision: str, workload: str) -> dict:
     if args.autotune:
         t = sim.autotune(5)
         log(f"autotuned tile: {t}")
-        return {"rows": t["tile_rows"], "planes": t["chunk_planes"], "chosen_by": "autotune"}
+        return {"rows": t["tile_rows"], "planes": t["chunk_planes"], "chosen_by": "autotune, unless the default was faster"}
     if not args.tile and workload != "tetrahedron_drop":
         return {"chosen_by": "library default"}
     rows, planes = (int(v) for v in args.tile.split(",")) if args.tile else DEFAULT_TILES[precision]

@@ -214,9 +214,11 @@ const char *pf_lbm_batch_last_error(const pf_lbm_batch *b);
 
 /* Autotuner of the tile shape of the fluid pass, which leaves the arithmetic unchanged: tiles of
  * 64 x 4 or 64 x 8 nodes (FP64 populations: 64 x 4) marching z-chunks of 4, 8, 16, 32 or 64
- * planes.  Each candidate runs 1 + steps_per_candidate steps of the simulation itself (the state
- * advances), timed with HIP events; the fastest is kept.  out3 (HOST, may be NULL): chosen tile
- * rows, chosen planes per chunk, its mean step time in ms. */
+ * planes, and the handle's present shape where that is none of them (the default has shorter chunks on
+ * small grids).  Each runs 1 + steps_per_candidate steps of the simulation itself (the state
+ * advances), timed with HIP events; the fastest is kept.  out3 (HOST, may be NULL): rows and planes of
+ * the fastest of the listed shapes and its mean step time in ms; the handle keeps its present shape
+ * where that was faster still. */
 int pf_lbm_autotune(pf_lbm *h, int32_t steps_per_candidate, double *out3);
 
 /* Tile shape of the fluid pass (as pf_lbm_autotune chooses it, or a shape kept from an earlier

@@ -139,7 +139,8 @@ class Simulation:
         return out
 
     def autotune(self, steps_per_candidate: int = 10) -> dict:
-        """Pick the fastest result-invariant launch shapes (advances the simulation)."""
+        """Pick the fastest result-invariant launch shapes (advances the simulation).  Returns the fastest
+        of the tuner's shapes; the present one stays where it was faster than all of them."""
         rc, out = B.pf_lbm_autotune(self._h, steps_per_candidate)
         self._check(rc)
         return {"tile_rows": int(out[0]), "chunk_planes": int(out[1]), "ms_per_step": out[2]}
