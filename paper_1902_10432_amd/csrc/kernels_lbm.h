@@ -631,16 +631,18 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY>(
 // search of eight nodes loaded in one round.
 constexpr int FORCE_WAVES = 12;  // waves per block of the force scan (one block per CU)
 
-// component d of direction i known only at run time, from two-bit fields
-__device__ __forceinline__ int dir_rt(int i, int d) {
+// component d of direction i known only at run time, from two-bit fields; i may reach 32 (the last lane of
+// a node's eight on D3Q27), where the shift by 64 wraps and the result is not used
+__host__ __device__ __forceinline__ constexpr int dir_rt(int i, int d) {
     constexpr auto pack = [](const int *c) {
         unsigned long long v = 0;
         for (int k = 0; k < 27; ++k) v |= (unsigned long long)(c[k] + 1) << (2 * k);
         return v;
     };
     constexpr unsigned long long X = pack(kCX), Y = pack(kCY), Z = pack(kCZ);
-    return (int)(((d == 0 ? X : (d == 1 ? Y : Z)) >> (2 * i)) & 3u) - 1;
+    return (int)(((d == 0 ? X : (d == 1 ? Y : Z)) >> ((2 * i) & 63)) & 3u) - 1;
 }
+static_assert(dir_rt(32, 0) == dir_rt(0, 0) && dir_rt(26, 2) == kCZ[26], "directions defined for every lane");
 
 // periodic wrap by repeated addition (usually none; several on an axis shorter than the offset)
 __device__ __forceinline__ int wrapl(int i, int n) {
