@@ -213,23 +213,23 @@ void pf_lbm_batch_destroy(pf_lbm_batch *b);
 const char *pf_lbm_batch_last_error(const pf_lbm_batch *b);
 
 /* Autotuner of the tile shape of the fluid pass, which leaves the arithmetic unchanged: tiles of
- * 64 x 4 or 64 x 8 nodes (FP64 populations: 64 x 4) marching z-chunks of 4, 8, 16, 32 or 64
- * planes, and the handle's present shape where that is none of them (the default has shorter chunks on
- * small grids).  Each runs 1 + steps_per_candidate steps of the simulation itself (the state
- * advances), timed with HIP events; the fastest is kept.  out3 (HOST, may be NULL): rows and planes of
- * the fastest of the listed shapes and its mean step time in ms; the handle keeps its present shape
- * where that was faster still. */
+ * 64 x 4 or 64 x 8 nodes (FP64 populations: 64 x 4; FP16 storage on D3Q19 also 64 x 16) marching
+ * z-chunks of 4, 8, 16, 32 or 64 planes, and the handle's present shape where that is none of them (the
+ * default has shorter chunks on small grids).  Each runs 1 + steps_per_candidate steps of the
+ * simulation itself (the state advances), timed with HIP events; the fastest is kept.  out3 (HOST, may be
+ * NULL): rows and planes of the fastest of the listed shapes and its mean step time in ms; the handle
+ * keeps its present shape where that was faster still. */
 int pf_lbm_autotune(pf_lbm *h, int32_t steps_per_candidate, double *out3);
 
 /* Tile shape of the fluid pass (as pf_lbm_autotune chooses it, or a shape kept from an earlier
- * tuning): tiles of 64 x rows nodes (rows 4 or 8; 4 with FP64 populations) marching z-chunks of
+ * tuning): tiles of 64 x rows nodes (rows as listed above) marching z-chunks of
  * planes >= 1 planes.  The arithmetic does not depend on it.  Errors: PF_LBM_EUNSUPPORTED (rows
  * not built for the precision and lattice), PF_LBM_EINVAL. */
 int pf_lbm_set_tile(pf_lbm *h, int32_t rows, int32_t planes);
 
 /* Entries of the per-step list of nodes that changed side (Sec. 3.2.2 node conversion) that the
  * handle uses, in [0, 65536] (the default, the list's size in the workspace).  When a step's
- * conversions exceed it, the conversion gather and the closing pass scan the whole bounding box of
+ * conversions exceed it, the conversion kernel scans the whole bounding box of
  * the phase fields instead of the list; the results are the same.  Lower values exist to run that
  * path on purpose (tests).  Errors: PF_LBM_EINVAL (out of range or NULL handle). */
 int pf_lbm_set_event_capacity(pf_lbm *h, int32_t entries);

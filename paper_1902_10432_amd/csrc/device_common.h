@@ -117,28 +117,7 @@ struct ClassifyPart {
     uint32_t icnt[PF_LBM_MAX_BODIES];  // per-body count of interface nodes phi_floor < phi < 1
 };
 
-// Deterministic sum of v[0..n) by one wave: lane l accumulates v[l + 64 m] into four
-// interleaved partial sums (independent loads in flight), combined in a fixed order, then a fixed
-// xor-shuffle tree across the lanes.
-__device__ __forceinline__ double wave_sum_array(const double *v, int n) {
-    const int lane = (int)(threadIdx.x & 63);
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int j = lane;
-    for (; j + 192 < n; j += 256) {
-        s0 += v[j];
-        s1 += v[j + 64];
-        s2 += v[j + 128];
-        s3 += v[j + 192];
-    }
-    for (; j < n; j += 64) s0 += v[j];
-    double s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s;
-}
-
-__device__ __forceinline__ double mimg(double d, double L) { return d - L * floor(d / L + 0.5); }
-// the same with a precomputed 1/L (hot loops)
+// minimum image of d on a period L, invL = 1 / L
 __device__ __forceinline__ double mimg_r(double d, double L, double invL) { return d - L * floor(d * invL + 0.5); }
 
 __device__ __forceinline__ int wrapi(int i, int n) {
@@ -234,7 +213,7 @@ struct Prm {
     T rho0;          // reference density of psi (the FP16 form's reference density uses it)
     T fext[3];
     int flags;       // PF_LBM_* step flags
-    double threshold, mobility, eta, r_c, n_exp, e0, R_A;
+    double threshold, mobility, eta, r_c, R_A;
     double phi_floor; // phase values at or below it count as absent (Sec. 3.3)
     double inv_n[3]; // 1 / nx, 1 / ny, 1 / nz
     int tn[3];       // phase-field tiles per axis (ceil(n / tile edge))
@@ -411,17 +390,7 @@ struct BoxIter {
             c[d] = v;
         }
     }
-    // does unwrapped coordinate v on axis d lie in the box (always, once the box spans the axis)
-    __device__ __forceinline__ bool inside(int d, int v) const {
-        return ext[d] >= n[d] || (v >= lo[d] && v < lo[d] + ext[d]);
-    }
 };
-
-// periodic wrap of i when it lies within one period of [0, n)
-__device__ __forceinline__ int wrap1(int i, int n) {
-    i += i < 0 ? n : 0;
-    return i - (i >= n ? n : 0);
-}
 
 // periodic wrap of i when it lies within two periods of [0, n) (offsets of up to 2 cells on axes
 // as short as one cell)

@@ -59,17 +59,6 @@ struct Nbr {
     }
 };
 
-// Rigid-body velocity V + omega x (p - X) at point p (minimum image), Sec. 3.1.1.
-template <typename T>
-__device__ __forceinline__ void wall_velocity(const Prm<T> &p, const BodyDev &B, double px, double py, double pz,
-                                              double &ux, double &uy, double &uz) {
-    const double rx = mimg_r(px - B.X[0], p.nx, p.inv_n[0]), ry = mimg_r(py - B.X[1], p.ny, p.inv_n[1]),
-                 rz = mimg_r(pz - B.X[2], p.nz, p.inv_n[2]);
-    ux = B.V[0] + (B.W[1] * rz - B.W[2] * ry);
-    uy = B.V[1] + (B.W[2] * rx - B.W[0] * rz);
-    uz = B.V[2] + (B.W[0] * ry - B.W[1] * rx);
-}
-
 // reciprocal: correctly rounded in FP64 (parity with the FP64 oracle), hardware rcp in FP32
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }

@@ -944,7 +944,7 @@ __device__ __forceinline__ T feq_dir(T rho, T ux, T uy, T uz) {
 
 // The 3x3x3 neighbourhood of a node, its 27 cell words loaded in one round and kept as bit sets
 // (bit k for offset k = (dz + 1) 9 + (dy + 1) 3 + (dx + 1); 13 is the node itself), for the
-// conversion tests of the gather kernel, which otherwise wait for memory once per neighbour.
+// conversion tests of k_convert, which otherwise wait for memory once per neighbour.
 struct Nbhd {
     uint32_t f2s_bits = 0, fluid_bits = 0;  // "became solid" mark; not solid
     cell_t centre;
@@ -1191,7 +1191,6 @@ __global__ void k_init_phi(Prm<T> p, const double *__restrict__ src, double *__r
     }
 }
 
-// fluid at rest: f = f_eq(rho, 0) = w_i rho on fluid nodes, 0 on solid nodes
 // fluid at rest: f = f_eq(rho, 0) = w_i rho on fluid nodes, 0 on solid nodes; psi_init gets the
 // pseudopotential of these populations (the reference of the FP16 form for the first step)
 template <typename S, class L>

@@ -673,14 +673,11 @@ __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ dZ, in
 // Mean-squared-error terms of the layer-by-layer path, 64 rows a block (one wave): dY = 2 (y - t) / n,
 // the FP64 sum of (y - t)^2 and the FP32 sum of dY
 __global__ __launch_bounds__(64) void k_loss(const float *__restrict__ y, const float *__restrict__ t, int n,
-                                             float *__restrict__ dy, __bf16 *__restrict__ dyb,
-                                             double *__restrict__ loss, float *__restrict__ dysum) {
+                                             __bf16 *__restrict__ dyb, double *__restrict__ loss,
+                                             float *__restrict__ dysum) {
     const int i = blockIdx.x * 64 + threadIdx.x;
     const float e = i < n ? y[i] - t[i] : 0.0f, g = 2.0f * e / (float)n;
-    if (i < n) {
-        dy[i] = g;
-        dyb[i] = (__bf16)g;
-    }
+    if (i < n) dyb[i] = (__bf16)g;
     double s = (double)e * e;
     float d = g;
 #pragma unroll
@@ -705,7 +702,7 @@ struct pf_mlp {
     LayerMap lm{};
     long long np = 0, nwb = 0;
     // workspace offsets
-    size_t P, G, Mo, Vo, Wb, Wt, Xb, Y, dY, dYb, loss, dA, dZ, dZb, Z[10], A[10];
+    size_t P, G, Mo, Vo, Wb, Wt, Xb, Y, dYb, loss, dA, dZ, dZb, Z[10], A[10];
     size_t dzl, part, dzsum, dysum, lossp;
     int max_chunks = 1;
     int adam_t = 0;
@@ -820,8 +817,8 @@ void finish_grads(pf_mlp *h, int n, int chunks, int blocks, float lr) {
 void run_backward(pf_mlp *h, const float *t, int n, int chunks, int chunk) {
     const LayerMap &lm = h->lm;
     const int H = h->cfg.hidden, L = lm.n - 1, nb = (n + 63) / 64;
-    k_loss<<<nb, 64, 0, h->stream>>>(at<float>(h, h->Y), t, n, at<float>(h, h->dY), at<__bf16>(h, h->dYb),
-                                     at<double>(h, h->lossp), at<float>(h, h->dysum));
+    k_loss<<<nb, 64, 0, h->stream>>>(at<float>(h, h->Y), t, n, at<__bf16>(h, h->dYb), at<double>(h, h->lossp),
+                                     at<float>(h, h->dysum));
     const __bf16 *dZb = at<__bf16>(h, h->dYb);
     const int tiles = ((H + 127) / 128) * ((H + 127) / 128);
     for (int l = L; l >= 0; --l) {
@@ -997,7 +994,6 @@ int pf_mlp_init(const pf_mlp_config *cfg, uint64_t seed, void *workspace, size_t
     tmp.Wt = take(2 * nwb);
     tmp.Xb = take(2 * B * cfg->n_in);
     tmp.Y = take(4 * B);
-    tmp.dY = take(4 * B);
     tmp.dYb = take(2 * B);
     tmp.loss = take(8);
     // error terms: layer by layer FP32 dA, two FP32 and two BF16 dZ; fused, one BF16 dZ a layer (at

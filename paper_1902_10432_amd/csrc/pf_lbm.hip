@@ -59,7 +59,7 @@ struct pf_lbm {
     char *ws = nullptr;
     Layout L{};
     long long N = 0, Np = 0;
-    int dense_blocks = 0, box_blocks = 1;
+    int dense_blocks = 0;
     int box_grid = 1, force_grid = 1;  // grids of the box kernels and of the force scan
     int cgrid = 1;  // classification partials written per step (grid of the phase update)
     // tile shape of the fluid pass, which leaves the arithmetic unchanged (pf_lbm_autotune): rows
@@ -267,8 +267,6 @@ Prm<T> make_prm(const pf_lbm *h) {
     p.mobility = h->cfg.mobility;
     p.eta = h->cfg.eta;
     p.r_c = h->cfg.r_c;
-    p.n_exp = h->cfg.n_exp;
-    p.e0 = h->cfg.e0;
     p.R_A = h->cfg.R_A;
     p.phi_floor = h->cfg.phi_floor;
     p.inv_n[0] = 1.0 / h->cfg.nx;
@@ -451,7 +449,7 @@ int enqueue_step(pf_lbm *h, double *parts = nullptr) {
 }
 
 template <typename S, class Lat>
-int init_device(pf_lbm *h, const pf_lbm_body *bodies_in, const double *rho0, const double *phi0,
+int init_device(pf_lbm *h, const double *rho0, const double *phi0,
                 const std::vector<BodyDev> &bodies, const StepState &st0) {
     using T = ArT<S>;
     const Prm<T> p = make_prm<T>(h);
@@ -462,7 +460,6 @@ int init_device(pf_lbm *h, const pf_lbm_body *bodies_in, const double *rho0, con
     StepState *st = (StepState *)(h->ws + h->L.state);
     const dim3 b(256);
     const int gd = std::max(1, std::min(h->dense_blocks, 65535));
-    (void)bodies_in;
     const size_t tab = sizeof(BodyDev) * std::max(h->nb, 1);
     HIPCHK(h, hipMemcpyAsync(h->ws + h->L.bodies, bodies.data(), tab, hipMemcpyHostToDevice, s));
     HIPCHK(h, hipMemcpyAsync(h->ws + h->L.bodies + tab, bodies.data(), tab, hipMemcpyHostToDevice, s));
@@ -638,7 +635,6 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
     h->N = N;
     h->Np = Np;
     h->dense_blocks = (int)((N + 255) / 256);
-    h->box_blocks = box_blocks;
     h->box_grid = box_grid;
     h->force_grid = force_grid;
     h->cgrid = cgrid;
@@ -693,12 +689,12 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
                     st0.rep_off[st0.n_rep++] = (dx + 8) | (dy + 8) << 8 | (dz + 8) << 16;
                 }
     }
-    int rc = h->q == 27 ? (h->prec == PF_LBM_FP64   ? init_device<double, D3Q27>(h, bodies, rho0, phi0, bd, st0)
-                           : h->prec == PF_LBM_FP32 ? init_device<float, D3Q27>(h, bodies, rho0, phi0, bd, st0)
-                                                    : init_device<half_t, D3Q27>(h, bodies, rho0, phi0, bd, st0))
-                        : (h->prec == PF_LBM_FP64   ? init_device<double, D3Q19>(h, bodies, rho0, phi0, bd, st0)
-                           : h->prec == PF_LBM_FP32 ? init_device<float, D3Q19>(h, bodies, rho0, phi0, bd, st0)
-                                                    : init_device<half_t, D3Q19>(h, bodies, rho0, phi0, bd, st0));
+    int rc = h->q == 27 ? (h->prec == PF_LBM_FP64   ? init_device<double, D3Q27>(h, rho0, phi0, bd, st0)
+                           : h->prec == PF_LBM_FP32 ? init_device<float, D3Q27>(h, rho0, phi0, bd, st0)
+                                                    : init_device<half_t, D3Q27>(h, rho0, phi0, bd, st0))
+                        : (h->prec == PF_LBM_FP64   ? init_device<double, D3Q19>(h, rho0, phi0, bd, st0)
+                           : h->prec == PF_LBM_FP32 ? init_device<float, D3Q19>(h, rho0, phi0, bd, st0)
+                                                    : init_device<half_t, D3Q19>(h, rho0, phi0, bd, st0));
     if (rc != PF_LBM_OK) {
         g_init_error = h->err;
         delete h;

@@ -151,7 +151,7 @@ class Simulation:
 
     def set_event_capacity(self, entries: int) -> None:
         """Entries of the per-step conversion event list in use; beyond them a step's conversion
-        passes scan the whole phase-field box (same results)."""
+        scans the whole phase-field box (same results)."""
         self._check(B.load_library().pf_lbm_set_event_capacity(self._h, int(entries)))
 
     def diag(self) -> dict:
