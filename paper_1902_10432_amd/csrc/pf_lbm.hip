@@ -301,9 +301,15 @@ int default_ty(int prec) { return prec == PF_LBM_FP32 ? 8 : 4; }
 // give every CU a block (61 x 45 x 50, FP32: 72 us a step with one plane, 83 with 4, 99 with 8), at
 // 128^3 the one round of 8 planes (171 us; 4: 176, 2: 188).  Large grids run at the memory rate, flat
 // between 8 and 16 planes (256^3 FP32: 4: 1032, 8: 962, 16: 967, 32: 989 us a step), and FP16 storage
-// loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).
-int default_tz(int nx, int ny, int nz, int ty, int per_cu) {
+// loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).  In FP64 the planes and halos read twice weigh
+// most, and the chunk is the longest power of two above 8 that leaves the grid 1024 blocks, where there is
+// one (fluid pass, 8 planes against the longer chunk: 64 x 64 x 1024 324 and 306 us with 16, 192^3 628 and
+// 610 with 16, 250^3 1504 and 1457 with 32; D3Q27 483 and 453, 935 and 905, 2193 and 2148).
+int default_tz(int prec, int nx, int ny, int nz, int ty, int per_cu) {
     const double tiles = (double)((nx + 63) / 64) * ((ny + ty - 1) / ty), slots = 256.0 * per_cu;
+    if (prec == PF_LBM_FP64)
+        for (int tz = 64; tz > 8; tz /= 2)
+            if (tiles * ((nz + tz - 1) / tz) >= 1024.0) return tz;
     auto cost = [&](int tz) {
         const double r = tiles * ((nz + tz - 1) / tz) / slots;
         return (r <= 1.0 ? 1.0 : r + 0.5) * (tz + 1.5);
@@ -645,7 +651,7 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
                                   : (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q19, 4>()
                                      : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q19, 8>()
                                                               : fluid_per_cu<half_t, D3Q19, 4>());
-    h->fluid_tz = default_tz(cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
+    h->fluid_tz = default_tz(h->prec, cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
     const int np1 = n_bodies + 1;
     h->sigma.assign((size_t)np1 * np1, 0.0);
     for (int a = 0; a < np1; ++a)
