@@ -303,11 +303,16 @@ template <int TY>
 struct FluidShape {
     static constexpr int W = TY <= 4 ? 4 : 8, RPT = TY / W;
 };
-// waves per SIMD that the registers have to allow: four where two 8-wave blocks fit a CU by their LDS
-// and the register count would otherwise end just above 128
+// FP32 D3Q27 tiles of 8 rows exist in two forms, as the register count ends just above 128: held to 128, so
+// that two blocks of 8 waves share a CU (LONE false), and free, one block a CU (LONE true).
 template <typename S, class L, int TY>
+constexpr bool fluid_two_forms() {
+    return L::Q == 27 && sizeof(S) == 4 && TY == 8;
+}
+// waves per SIMD that the registers have to allow
+template <typename S, class L, int TY, bool LONE>
 constexpr int fluid_min_waves() {
-    return L::Q == 27 && sizeof(S) == 4 && TY == 8 ? 4 : 1;
+    return fluid_two_forms<S, L, TY>() && !LONE ? 4 : 1;
 }
 constexpr size_t FLUID_LDS_MAX = 80 * 1024;
 template <typename S, class L, int TY>
@@ -357,8 +362,8 @@ __device__ __forceinline__ ArT<S> node_psi_of(const Prm<ArT<S>> &p, const BodyDe
 // and event flag from the previous reclassification (publish_step_state): that reduction chain runs
 // beside the tiles instead of costing a launch, or, on a small grid where every tile runs at once,
 // instead of delaying the block that would run it first.
-template <typename S, class L, int TY>
-__global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY>())) void k_collide_stream(Prm<ArT<S>> p, const S *__restrict__ fin,
+template <typename S, class L, int TY, bool LONE>
+__global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY, LONE>())) void k_collide_stream(Prm<ArT<S>> p, const S *__restrict__ fin,
                                                                      S *__restrict__ fout, ArT<S> *__restrict__ psi,
                                                                      ArT<S> *__restrict__ psi_prev,
                                                                      const cell_t *__restrict__ mask, BodyDev *bodies,

@@ -295,19 +295,30 @@ bool fluid_ty_ok(int ty) {
 // spheres, FP16: 744 us a step with 4 rows, 862 with 8, 864 with 16).
 int default_ty(int prec) { return prec == PF_LBM_FP32 ? 8 : 4; }
 
+// FP32 D3Q27 in tiles of 8 rows: one block a CU on large grids, from planes of 40000 nodes, and where rows fill
+// their tiles of 64 from 6 million nodes.  Two hide the latency better, but have twice the planes in flight in
+// an XCD's L2, so that halo rows and the planes that chunks share are read from memory again (256^3: 2.45
+// instead of 2.08 GB a pass).  Four-sphere drop, two blocks against one, each with its chunk: 160^3 429 and 448
+// us a step, 200^3 765 and 806, 224^3 980 and 953, 256 x 256 x 128 727 and 666, 256^3 1559 and 1309;
+// 256 x 140 x 140 465 and 509, 256 x 128 x 256 729 and 678, 240 x 140 x 240 675 and 743.
+bool fluid_lone(int prec, int q, int nx, int ny, int nz) {
+    const long long plane = (long long)nx * ny;
+    return prec == PF_LBM_FP32 && q == 27 && (plane > 40000 || (nx % 64 == 0 && nx > 64 && plane * nz > 6000000));
+}
+
 // Default planes per z-chunk.  A block's time is about tz + 1.5 planes (two more planes of psi), and
 // the card holds 256 * per_cu blocks at once, so the chunk is the one of least rounds * (tz + 1.5),
 // with half a round for the tail where there is more than one: on small grids short chunks that
 // give every CU a block (61 x 45 x 50, FP32: 72 us a step with one plane, 83 with 4, 99 with 8), at
 // 128^3 the one round of 8 planes (171 us; 4: 176, 2: 188).  Large grids run at the memory rate, flat
-// between 8 and 16 planes (256^3 FP32: 4: 1032, 8: 962, 16: 967, 32: 989 us a step), and FP16 storage
-// loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).  In FP64 the planes and halos read twice weigh
-// most, and the chunk is the longest power of two above 8 that leaves the grid 1024 blocks, where there is
-// one (fluid pass, 8 planes against the longer chunk: 64 x 64 x 1024 324 and 306 us with 16, 192^3 628 and
-// 610 with 16, 250^3 1504 and 1457 with 32; D3Q27 483 and 453, 935 and 905, 2193 and 2148).
-int default_tz(int prec, int nx, int ny, int nz, int ty, int per_cu) {
+// between 8 and 16 planes (256^3 FP32, four spheres: 4: 1032, 8: 962, 16: 967, 32: 989 us a step), and FP16
+// storage loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).  In FP64 and in the one-block form of FP32 D3Q27 the planes and halos read twice weigh most, and the chunk is the longest power of two
+// above 8 that leaves the grid 1024 blocks, where there is one (fluid pass in FP64, 8 planes against the
+// longer chunk: 64 x 64 x 1024 324 and 306 us with 16, 192^3 628 and 610 with 16, 250^3 1504 and 1457 with 32;
+// on D3Q27 483 and 453, 935 and 905, 2193 and 2148; FP32 D3Q27 256^3 1363 and 1309 with 32).
+int default_tz(int prec, int q, int nx, int ny, int nz, int ty, int per_cu) {
     const double tiles = (double)((nx + 63) / 64) * ((ny + ty - 1) / ty), slots = 256.0 * per_cu;
-    if (prec == PF_LBM_FP64)
+    if (prec == PF_LBM_FP64 || fluid_lone(prec, q, nx, ny, nz))
         for (int tz = 64; tz > 8; tz /= 2)
             if (tiles * ((nz + tz - 1) / tz) >= 1024.0) return tz;
     auto cost = [&](int tz) {
@@ -321,10 +332,10 @@ int default_tz(int prec, int nx, int ny, int nz, int ty, int per_cu) {
 }
 
 // blocks of the default fluid-pass tile that a CU holds at once (LDS and registers)
-template <typename S, class Lat, int TY>
+template <typename S, class Lat, int TY, bool LONE = false>
 int fluid_per_cu() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)k_collide_stream<S, Lat, TY>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)k_collide_stream<S, Lat, TY, LONE>,
                                                      64 * FluidShape<TY>::W, 0) != hipSuccess) {
         (void)hipGetLastError();
         n = 2;
@@ -340,8 +351,13 @@ void launch_fluid_ty(pf_lbm *h, const Prm<ArT<S>> &p, const S *fc, S *fn, ArT<S>
         const int tz = h->fluid_tz;
         const unsigned tiles = (unsigned)(((h->cfg.nx + 63) / 64) * ((h->cfg.ny + TY - 1) / TY));
         const unsigned chunks = (unsigned)((h->cfg.nz + tz - 1) / tz);
-        k_collide_stream<S, Lat, TY><<<dim3(tiles * chunks + (cpart ? 1 : 0)), dim3(64 * FluidShape<TY>::W), 0, h->stream>>>(
-            p, fc, fn, psi, psi_prev, mask, cur, par, st, cpart, h->cgrid, nbw, tz);
+        auto launch = [&](auto kernel) {
+            kernel<<<dim3(tiles * chunks + (cpart ? 1 : 0)), dim3(64 * FluidShape<TY>::W), 0, h->stream>>>(
+                p, fc, fn, psi, psi_prev, mask, cur, par, st, cpart, h->cgrid, nbw, tz);
+        };
+        if constexpr (fluid_two_forms<S, Lat, TY>())
+            if (fluid_lone(h->prec, h->q, h->cfg.nx, h->cfg.ny, h->cfg.nz)) return launch(k_collide_stream<S, Lat, TY, true>);
+        launch(k_collide_stream<S, Lat, TY, false>);
     }
 }
 
@@ -646,12 +662,14 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
     h->cgrid = cgrid;
     h->fluid_ty = default_ty(cfg->precision);
     const int per_cu = h->q == 27 ? (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q27, 4>()
-                                     : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q27, 8>()
+                                     : h->prec == PF_LBM_FP32 ? (fluid_lone(h->prec, h->q, cfg->nx, cfg->ny, cfg->nz)
+                                                                     ? fluid_per_cu<float, D3Q27, 8, true>()
+                                                                     : fluid_per_cu<float, D3Q27, 8>())
                                                               : fluid_per_cu<half_t, D3Q27, 4>())
                                   : (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q19, 4>()
                                      : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q19, 8>()
                                                               : fluid_per_cu<half_t, D3Q19, 4>());
-    h->fluid_tz = default_tz(h->prec, cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
+    h->fluid_tz = default_tz(h->prec, h->q, cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
     const int np1 = n_bodies + 1;
     h->sigma.assign((size_t)np1 * np1, 0.0);
     for (int a = 0; a < np1; ++a)
