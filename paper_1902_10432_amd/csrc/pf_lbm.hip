@@ -312,11 +312,13 @@ bool fluid_lone(int prec, int q, int nx, int ny, int nz) {
 // give every CU a block (61 x 45 x 50, FP32: 72 us a step with one plane, 83 with 4, 99 with 8), at
 // 128^3 the one round of 8 planes (171 us; 4: 176, 2: 188).  Large grids run at the memory rate, flat
 // between 8 and 16 planes (256^3 FP32, four spheres: 4: 1032, 8: 962, 16: 967, 32: 989 us a step), and FP16
-// storage loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us).  In FP64 and in the one-block form of FP32 D3Q27 the planes and halos read twice weigh most, and the chunk is the longest power of two
+// storage loses beyond 8 (192 x 176 x 168: 4: 325, 8: 339, 16: 383 us); a fluid without bodies still gains
+// from 16 (256^3 FP32 8: 742, 16: 704 us, FP16 storage on D3Q27 802 and 759).  In FP64 and in the one-block
+// form of FP32 D3Q27 the planes and halos read twice weigh most, and the chunk is the longest power of two
 // above 8 that leaves the grid 1024 blocks, where there is one (fluid pass in FP64, 8 planes against the
 // longer chunk: 64 x 64 x 1024 324 and 306 us with 16, 192^3 628 and 610 with 16, 250^3 1504 and 1457 with 32;
 // on D3Q27 483 and 453, 935 and 905, 2193 and 2148; FP32 D3Q27 256^3 1363 and 1309 with 32).
-int default_tz(int prec, int q, int nx, int ny, int nz, int ty, int per_cu) {
+int default_tz(int prec, int q, int nb, int nx, int ny, int nz, int ty, int per_cu) {
     const double tiles = (double)((nx + 63) / 64) * ((ny + ty - 1) / ty), slots = 256.0 * per_cu;
     if (prec == PF_LBM_FP64 || fluid_lone(prec, q, nx, ny, nz))
         for (int tz = 64; tz > 8; tz /= 2)
@@ -326,8 +328,8 @@ int default_tz(int prec, int q, int nx, int ny, int nz, int ty, int per_cu) {
         return (r <= 1.0 ? 1.0 : r + 0.5) * (tz + 1.5);
     };
     int best = 1;
-    for (int tz : {2, 3, 4, 6, 8})
-        if (cost(tz) < cost(best)) best = tz;
+    for (int tz : {2, 3, 4, 6, 8, 16})
+        if (cost(tz) < cost(best) && (tz <= 8 || nb == 0)) best = tz;
     return best;
 }
 
@@ -669,7 +671,7 @@ int pf_lbm_init(const pf_lbm_config *cfg, int32_t n_bodies, const pf_lbm_body *b
                                   : (h->prec == PF_LBM_FP64   ? fluid_per_cu<double, D3Q19, 4>()
                                      : h->prec == PF_LBM_FP32 ? fluid_per_cu<float, D3Q19, 8>()
                                                               : fluid_per_cu<half_t, D3Q19, 4>());
-    h->fluid_tz = default_tz(h->prec, h->q, cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
+    h->fluid_tz = default_tz(h->prec, h->q, n_bodies, cfg->nx, cfg->ny, cfg->nz, h->fluid_ty, per_cu);
     const int np1 = n_bodies + 1;
     h->sigma.assign((size_t)np1 * np1, 0.0);
     for (int a = 0; a < np1; ++a)
