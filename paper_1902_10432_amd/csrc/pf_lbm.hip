@@ -987,7 +987,8 @@ int pf_lbm_step_batch(pf_lbm *const *handles, int32_t n, int32_t n_steps) {
     // runs of 16 steps (eight captured pairs) round robin over the instances: each handle launches on
     // its own stream, so the launches of different instances queue side by side and their kernels
     // overlap.  Longer runs change less often between the streams that share a hardware queue: twelve
-    // bridges of 48 to 128 cells an edge, 32 steps, in runs of 2: 19.8 ms, 4: 19.4, 8 and 16: 19.3.
+    // bridges of 48 to 128 cells an edge, 32 steps without read-outs, in runs of 2: 19.7 ms, 4: 19.6, 8: 19.4,
+    // 16 and 32: 19.3.
     constexpr int RUN = 16;
     for (int done = 0; done < n_steps; done += RUN) {
         const int chunk = std::min(RUN, n_steps - done);
