@@ -24,9 +24,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // remainder, then the special cases (d infinite, n infinite or NaN).  It is the IEEE division without the
 // scaling for small d and without the second correction, half its instructions.  The factor 1/4 changes no
 // bit of the result and keeps the reciprocal of the largest finite d normal, as the hardware flushes
-// subnormal ones to zero (without it SiLU is 0 below z = -87.3, where it is about -1e-36; it costs 0.8 us
-// of 31 on 65536 rows of 4 -> 128 x 4 -> 1).  With the remainder exact the result differs from the correctly
-// rounded quotient in about one of 10^7 cases, by one unit in the last place.
+// subnormal ones to zero (without it SiLU is 0 below z = -87.3, where it is about -1e-36; 65536 rows of
+// 4 -> 128 x 4 -> 1 take 31.7 us with it and 31.6 without).  With the remainder exact the result differs from
+// the correctly rounded quotient in about one of 10^7 cases, by one unit in the last place.
 __device__ __forceinline__ float quotient(float n4, float d4) {
     const float r = __builtin_amdgcn_rcpf(d4), q = n4 * r;
     return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d4, q, n4), r, q), d4, n4);
@@ -36,16 +36,17 @@ __device__ __forceinline__ float scalar(float k) {
     asm("" : "+s"(k));
     return k;
 }
-__device__ __forceinline__ float quarter() { return scalar(0.25f); }
-// (1 + e) / 4
-__device__ __forceinline__ float plus_one4(float e) { return __builtin_fmaf(e, quarter(), quarter()); }
-__device__ __forceinline__ float silu(float z) { return quotient(quarter() * z, plus_one4(__expf(-z))); }
-// the same from z / 4 (the factor of the base-2 exponent takes the 4)
-__device__ __forceinline__ float silu4(float z4) {
-    return quotient(z4, plus_one4(__builtin_amdgcn_exp2f(z4 * scalar(-4.0f * 0x1.715476p+0f))));
+// z / (1 + exp(-z)) from z4 = z / 4, with quarter = 1/4 and c = -4 log2(e)
+__device__ __forceinline__ float silu4(float z4, float quarter, float c) {
+    return quotient(z4, __builtin_fmaf(__builtin_amdgcn_exp2f(z4 * c), quarter, quarter));
+}
+constexpr float SILU_C = -4.0f * 0x1.715476p+0f;
+__device__ __forceinline__ float silu(float z) {
+    const float quarter = scalar(0.25f);
+    return quotient(quarter * z, __builtin_fmaf(__expf(-z), quarter, quarter));
 }
 __device__ __forceinline__ float silu_grad(float z) {
-    const float s = quotient(0.25f, plus_one4(__expf(-z)));
+    const float quarter = scalar(0.25f), s = quotient(0.25f, __builtin_fmaf(__expf(-z), quarter, quarter));
     return s * (1.0f + z * (1.0f - s));
 }
 
@@ -256,6 +257,7 @@ __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, 
         if (r0 >= M) return;  // whole block
     }
     const int L = lm.n - 1;
+    const float quarter = scalar(0.25f), silu_c = scalar(SILU_C);
     auto feat = [&](int t) { return 16 * (wave * NT + t); };  // first column of this wave's tile t
     // this wave's slice of a square layer's weights, row-major [H][H]
     auto load_w = [&](const __bf16 *W, bf16x8 (&w)[NT][KS]) {
@@ -264,11 +266,12 @@ __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, 
 #pragma unroll
             for (int k = 0; k < KS; ++k) w[t][k] = *(const bf16x8 *)(W + (feat(t) + rl) * H + 32 * k + kq);
     };
+    // biases, inference a quarter of them
     auto load_b = [&](int l, f32x4 (&bias)[NT]) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bias[t][r] = P[lm.b[l] + feat(t) + fq + r];
+            for (int r = 0; r < 4; ++r) bias[t][r] = (TRAIN ? 1.0f : quarter) * P[lm.b[l] + feat(t) + fq + r];
     };
     // pre-activations -> BF16 activations in LDS buffer c (and, training, Z and A)
     auto activate = [&](int l, int c, int s, const f32x4 (&acc)[NT], const f32x4 (&bias)[NT]) {
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(256) void k_mlp_fused(const float *__restrict__ x, 
                     z[r] = acc[t][r] + bias[t][r];
                     v[r] = (__bf16)silu(z[r]);
                 } else {  // z / 4 in the one rounding of the sum
-                    v[r] = (__bf16)silu4(__builtin_fmaf(acc[t][r], quarter(), quarter() * bias[t][r]));
+                    v[r] = (__bf16)silu4(__builtin_fmaf(acc[t][r], quarter, bias[t][r]), quarter, silu_c);
                 }
             }
             *(bf16x4 *)&act[c][16 * s + rl][feat(t) + fq] = v;
