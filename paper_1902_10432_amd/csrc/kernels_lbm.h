@@ -108,7 +108,8 @@ struct WallMot {
 // psin(I): psi of the neighbour in direction I; FP16 form: refn(I) its reference density R (the
 // encode of a population pushed there) and rown the node's own (the encode of its own slots),
 // both R(psi) of this step's psi, formed once per node with the window
-template <typename S, class L, typename PsiN, typename RefN>
+// SUM: the density for the force scan is summed for every node (see there)
+template <typename S, class L, bool SUM, typename PsiN, typename RefN>
 __device__ __forceinline__ void collide_push(const Prm<ArT<S>> &p, const S *sv, ArT<S> rin, PsiN psin, RefN refn,
                                              ArT<S> psi0, ArT<S> rown, S *__restrict__ fout, uint32_t solid_dirs,
                                              int x, int y, int z, long long Np, const WallMot *wm,
@@ -124,14 +125,15 @@ __device__ __forceinline__ void collide_push(const Prm<ArT<S>> &p, const S *sv, 
     sfor<L::Q>([&](auto I) { f[I] = pop_get<S>(sv[I], Dir<decltype(I)::value, L>::template w<T>(), rin); });
     // The density of a node with links for the moving-wall term of the force scan, which would read the q
     // populations again for it.  FP32: summed in the order of the directions, as the scan would (the sums
-    // on the bodies cancel to far below its rounding).  FP64 stores the collision's own with the streaming,
-    // so that no branch waits for the neighbour bits here.
-    if constexpr (sizeof(S) == 4)
-        if (solid_dirs) {
-            T r = T(0);
-            sfor<L::Q>([&](auto I) { r += f[I]; });
-            stb(rho_link, idx * (uint32_t)sizeof(T), r);
-        }
+    // on the bodies cancel to far below its rounding), here where a node has links, or (SUM) for every node
+    // and stored with the streaming, so that no branch waits for the neighbour bits here.  FP64 stores the
+    // collision's own there.
+    T rlink = T(0);
+    if constexpr (sizeof(S) == 4) {
+        if (SUM || solid_dirs) sfor<L::Q>([&](auto I) { rlink += f[I]; });
+        if constexpr (!SUM)
+            if (solid_dirs) stb(rho_link, idx * (uint32_t)sizeof(T), rlink);
+    }
     // moments from pair sums and differences
     T rho = f[0], jx = T(0), jy = T(0), jz = T(0);
     sfor<(L::Q - 1) / 2>([&](auto K) {
@@ -213,7 +215,7 @@ __device__ __forceinline__ void collide_push(const Prm<ArT<S>> &p, const S *sv, 
         });
     } else if constexpr (!wall_in_fluid_pass<S>()) {
         // f*_i into slot opp(i); the force scan adds the moving-wall term and the mass correction
-        if constexpr (sizeof(S) == 8) stb(rho_link, idx * (uint32_t)sizeof(T), rho);
+        if constexpr (SUM || sizeof(S) == 8) stb(rho_link, idx * (uint32_t)sizeof(T), SUM ? rlink : rho);
         sfor<L::Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (i > 0) {
@@ -517,9 +519,9 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY, 
 
     // D3Q27: the neighbour-bit words of the plane being collided are loaded ahead of plane z + 2, as the
     // collision needs them first and loads are waited for in their order (FP32, 64^3: 42.1 -> 39.8 us,
-    // 130^3: 209 -> 203).  In FP64, where they are needed only for streaming, behind it (64^3 in chunks of
-    // 8 planes: 45.2 us, loaded ahead 48.5).
-    constexpr bool NBPRE = !L::kBits && sizeof(S) < 8;
+    // 130^3: 209 -> 203).  In FP64 and in the one-block form, where they are needed only for streaming, behind
+    // it (FP64 64^3 in chunks of 8 planes: 45.2 us, loaded ahead 48.5; one block, 250^3: 977 and 1012).
+    constexpr bool NBPRE = !L::kBits && sizeof(S) < 8 && !LONE;
     NodeIn<S, L> A[RPT], B[RPT];
     // prologue: psi of planes zs - 1 and zs, populations of plane zs into LDS, plane zs + 1 in
     // flight
@@ -595,7 +597,7 @@ __global__ __launch_bounds__(64 * FluidShape<TY>::W, (fluid_min_waves<S, L, TY, 
                         constexpr int o = Dir<i, L>::y * 66 + Dir<i, L>::x;
                         return Dir<i, L>::z < 0 ? rm[o] : (Dir<i, L>::z > 0 ? rp[o] : r0[o]);
                     };
-                    collide_push<S, L>(
+                    collide_push<S, L, LONE>(
                         p, cur, rin, [&](auto I) { return win_psi<S>(nbr(I)); },
                         [&](auto I) { return win_ref<S>(nbr(I)); }, psi0, win_ref<S>(*r0), fout, solid_dirs, x,
                         y0 + ty, z, plane_stride(), wall_mot(), psi_prev);

@@ -295,15 +295,18 @@ bool fluid_ty_ok(int ty) {
 // spheres, FP16: 744 us a step with 4 rows, 862 with 8, 864 with 16).
 int default_ty(int prec) { return prec == PF_LBM_FP32 ? 8 : 4; }
 
-// FP32 D3Q27 in tiles of 8 rows: one block a CU on large grids, from planes of 40000 nodes, and where rows fill
-// their tiles of 64 from 6 million nodes.  Two hide the latency better, but have twice the planes in flight in
-// an XCD's L2, so that halo rows and the planes that chunks share are read from memory again (256^3: 2.45
-// instead of 2.08 GB a pass).  Four-sphere drop, two blocks against one, each with its chunk: 160^3 429 and 448
-// us a step, 200^3 765 and 806, 224^3 980 and 953, 256 x 256 x 128 727 and 666, 256^3 1559 and 1309;
-// 256 x 140 x 140 465 and 509, 256 x 128 x 256 729 and 678, 240 x 140 x 240 675 and 743.
+// FP32 D3Q27 in tiles of 8 rows: one block a CU on large grids, from 6 million nodes where rows fill their
+// tiles of 64 and from 9.5 million where they fill three quarters.  Two hide the latency better, but have twice the
+// planes in flight in an XCD's L2, so that halo rows and the planes that chunks share are read from memory again
+// (256^3: 2.45 instead of 2.08 GB a pass); rows that leave lanes idle ask for less.  Two blocks against one, each
+// with its chunk, us a step: four-sphere drop 160^3 429 and 448, 200^3 765 and 806, 224^3 980 and 953, 256 x 256 x
+// 128 727 and 666, 256^3 1559 and 1309; two spheres 228 x 156 x 287 890 and 843, 200 x 200 x 300 1046 and 1027,
+// 240 x 140 x 240 712 and 749, 130 x 300 x 300 1024 and 1109.
 bool fluid_lone(int prec, int q, int nx, int ny, int nz) {
-    const long long plane = (long long)nx * ny;
-    return prec == PF_LBM_FP32 && q == 27 && (plane > 40000 || (nx % 64 == 0 && nx > 64 && plane * nz > 6000000));
+    const long long nodes = (long long)nx * ny * nz;
+    const int width = (nx + 63) / 64 * 64;
+    return prec == PF_LBM_FP32 && q == 27 &&
+           ((nx == width && nx > 64 && nodes > 6000000) || (4 * nx >= 3 * width && nx > 64 && nodes > 9500000));
 }
 
 // Default planes per z-chunk.  A block's time is about tz + 1.5 planes (two more planes of psi), and
@@ -320,7 +323,8 @@ bool fluid_lone(int prec, int q, int nx, int ny, int nz) {
 // on D3Q27 483 and 453, 935 and 905, 2193 and 2148; FP32 D3Q27 256^3 1363 and 1309 with 32).
 int default_tz(int prec, int q, int nb, int nx, int ny, int nz, int ty, int per_cu) {
     const double tiles = (double)((nx + 63) / 64) * ((ny + ty - 1) / ty), slots = 256.0 * per_cu;
-    if (prec == PF_LBM_FP64 || fluid_lone(prec, q, nx, ny, nz))
+    const bool lone = fluid_lone(prec, q, nx, ny, nz);
+    if (prec == PF_LBM_FP64 || lone)
         for (int tz = 64; tz > 8; tz /= 2)
             if (tiles * ((nz + tz - 1) / tz) >= 1024.0) return tz;
     auto cost = [&](int tz) {
@@ -329,7 +333,7 @@ int default_tz(int prec, int q, int nb, int nx, int ny, int nz, int ty, int per_
     };
     int best = 1;
     for (int tz : {2, 3, 4, 6, 8, 16})
-        if (cost(tz) < cost(best) && (tz <= 8 || nb == 0)) best = tz;
+        if (cost(tz) < cost(best) && (tz <= 8 || (nb == 0 && !lone))) best = tz;
     return best;
 }
 
